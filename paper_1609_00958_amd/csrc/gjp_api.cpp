@@ -302,6 +302,64 @@ static bool columns_share_inplane_setup(const gjp_geometry& g) {
   return true;
 }
 
+// Largest number of detector rows that any tile of the tile adjoint
+// (gjp_adjoint_tiles.hip) needs of a view, for 64 and 128 voxels along axis 2;
+// false if the geometry is not one it handles: column geometries in which every
+// source lies in front of all tiles (tiles reach up to 16 voxels past the
+// grid's upper ends), seen from every column.
+static bool tile_rows(const gjp_geometry& g, double rows[2]) {
+  rows[0] = rows[1] = 0.0;
+  if (!g.separable) return false;
+  const double kOver = 20.0;  // tile overhang plus margin (voxels)
+  for (int v = 0; v < g.n_views; ++v) {
+    const double* o = g.views_grid.data() + 12 * (size_t)v;
+    const double b1 = fabs(o[11]);
+    if (!(b1 > 0.0)) return false;
+    double b_min = b1, near = 1.0e30, z_far = 1.0;
+    if (g.beam == GJP_CONE) {
+      const float* P = g.proj.data() + 12 * (size_t)v;
+      double w_lo = 1.0e300, w_hi = 0.0;
+      for (int k = 0; k < 4; ++k) {
+        const double x = (k & 1) ? g.n[0] + kOver : -3.0, y = (k & 2) ? g.n[1] + kOver : -3.0;
+        const double w = (double)P[8] * x + (double)P[9] * y + (double)P[11];
+        w_lo = std::min(w_lo, w);
+        w_hi = std::max(w_hi, fabs(w));
+      }
+      if (!(w_lo > 1.0e-3 * w_hi)) return false;
+      bool used[2] = {false, false};
+      double r_lo[2] = {1.0e300, 1.0e300}, r_hi[2] = {-1.0e300, -1.0e300}, r_abs[2] = {0.0, 0.0};
+      for (int iu = 0; iu < g.n_u; ++iu) {
+        const double r[2] = {o[3] + (double)iu * o[6] - o[0], o[4] + (double)iu * o[7] - o[1]};
+        const int m = fabs(r[1]) > fabs(r[0]) ? 1 : 0;
+        used[m] = true;
+        r_lo[m] = std::min(r_lo[m], r[m]);
+        r_hi[m] = std::max(r_hi[m], r[m]);
+        for (int k = 0; k < 2; ++k) r_abs[k] = std::max(r_abs[k], fabs(r[k]));
+      }
+      for (int m = 0; m < 2; ++m) {
+        if (!used[m]) continue;
+        double d;
+        if (o[m] < -3.0 && r_lo[m] > 0.0)
+          d = -o[m];
+        else if (o[m] > g.n[m] + kOver && r_hi[m] < 0.0)
+          d = o[m] - (g.n[m] + kOver - 3.0);
+        else
+          return false;
+        near = std::min(near, d);
+        z_far = std::max(fabs(o[2] + 2.0), fabs(g.n[2] + 130.0 - o[2]));
+        b_min = std::min(b_min, b1 * d / r_abs[m]);
+      }
+    }
+    // a tile's own extent, plus how far its rows shift over its planes and
+    // columns (cone: the spread of the magnification at the far end of axis 2;
+    // parallel: rays climb less than one voxel per plane)
+    const double shift = g.beam == GJP_CONE ? 64.0 * z_far / near : 64.0;
+    for (int k = 0; k < 2; ++k)
+      rows[k] = std::max(rows[k], (64.0 * (k + 1) + 3.0 + shift) / b_min + 8.0);
+  }
+  return true;
+}
+
 extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geometry** out) {
   if (!d || !out) return fail(GJP_EINVAL, "gjp_create_geometry: null pointer");
   *out = nullptr;
@@ -381,6 +439,9 @@ extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geomet
     detector_projection(o, d->beam, g->proj.data() + 12 * v);
   }
   g->separable = columns_share_inplane_setup(*g);
+  double rows[2];
+  g->tiles = tile_rows(*g, rows) && rows[0] <= gjp::kTileMaxRows;
+  for (int k = 0; k < 2; ++k) g->tile_rows[k] = g->tiles ? (int)std::min(rows[k], 1.0e9) : 0;
   *out = g.release();
   return GJP_OK;
 }
@@ -968,6 +1029,36 @@ extern "C" gjp_status gjp_get_forward_tile(const gjp_geometry* g, int32_t vol_dt
 // Views per launch of the column-form gather (see gjp_back_project).
 static const int kGatherViews = 32;
 
+// The tile adjoint over chunks of views (scaled rays: one sinogram's bytes per
+// chunk, at most kTileScratch or one view).
+static const size_t kTileScratch = (size_t)2 << 30;
+
+static gjp_status back_project_tiles(const gjp_geometry* g, const double* d_views,
+                                     const float* d_proj, const float* d_sino, float* d_vol,
+                                     hipStream_t s) {
+  const size_t per_view = (size_t)g->n_u * (size_t)g->n_v * sizeof(float);
+  const long long chunk =
+      std::min<long long>(g->n_views, std::max<long long>(1, (long long)(kTileScratch / per_view)));
+  const size_t vol = (size_t)g->n[0] * g->n[1] * g->n[2] * sizeof(float);
+  const int splits = gjp::adjoint_tile_splits(g->n, (int)chunk);
+  const size_t bytes = (((size_t)chunk * per_view + 255) & ~(size_t)255) + 2 * splits * vol;
+  void* rays = nullptr;
+  GJP_HIP(scratch_alloc(&rays, bytes, s), "back_project: scaled rays");
+  int st = GJP_OK;
+  for (int v0 = 0; v0 < g->n_views && st == GJP_OK; v0 += (int)chunk) {
+    const int nc = (int)std::min<long long>(chunk, g->n_views - v0);
+    st = gjp::launch_adjoint_value_table(g, d_views, d_sino, v0, nc, static_cast<float*>(rays),
+                                         nullptr, nullptr, s);
+    if (st == GJP_OK)
+      st = gjp::launch_adjoint_gather(g, d_proj, nullptr, nullptr, static_cast<float*>(rays),
+                                      nullptr, nullptr, v0, 0, nc, v0 > 0, d_vol, s);
+  }
+  const hipError_t e = scratch_free(rays, s);
+  if (st != GJP_OK) return (gjp_status)st;
+  if (e != hipSuccess) return hip_fail(e, "back_project: free scaled rays");
+  return GJP_OK;
+}
+
 extern "C" gjp_status gjp_back_project(const gjp_geometry* g, const float* d_sino, float* d_vol,
                                        void* stream) {
   if (!g) return fail(GJP_EINVAL, "back_project: geometry is null");
@@ -979,6 +1070,7 @@ extern "C" gjp_status gjp_back_project(const gjp_geometry* g, const float* d_sin
   const float* d_proj = nullptr;
   int st = gjp::geometry_device(g, &d_views, &d_proj);
   if (st != GJP_OK) return (gjp_status)st;
+  if (g->tiles) return back_project_tiles(g, d_views, d_proj, d_sino, d_vol, s);
   // Table layouts: column geometries without clipping take the value table
   // (4 bytes per ray, positions from each column's affine map), other column
   // geometries the 16-byte ray table, the rest the 32-byte general table.

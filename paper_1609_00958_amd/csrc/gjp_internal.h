@@ -27,6 +27,10 @@ struct gjp_geometry {
   // the rays of a detector column share their in-plane coefficients, and the
   // adjoint uses the column-form gather.
   bool separable = false;
+  // The adjoint runs as launch_adjoint_tiles, whose tiles of 64 and 128 voxels
+  // along axis 2 need at most tile_rows[0] and tile_rows[1] detector rows.
+  bool tiles = false;
+  int tile_rows[2] = {0, 0};
 
   // device copies, per device (created on first use)
   struct Dev {
@@ -54,6 +58,30 @@ void timing_end(const char* name, TimedLaunch& t, hipStream_t s);
 // Empty entries after each detector column in the column-form ray table
 // (lets the adjoint read fixed-length candidate lists past a column's end).
 constexpr int kColumnPad = 8;
+
+// The tile adjoint (gjp_adjoint_tiles.hip): voxels of a tile along axes 0 and 1,
+// and the detector rows of one column that it can stage.
+constexpr int kTileEdge = 8;
+constexpr int kTileMaxRows = 7000;
+
+// View splits of the tile adjoint. Both axes in one launch, and the views split
+// so that it has about two rounds of workgroups (four per compute unit), with
+// at least six views each (a split costs a partial volume's write and read):
+// 64^3 / 64 views 193 us as two launches, 103, 62, 52, 48 and 57 us with 1, 2,
+// 4, 8 and 16 splits; 128^3 / 12 views 76 us, then 58, 55 and 65 us with 1, 2
+// and 4. Partial volumes of more than 128 MB: 0, two launches into the volume
+// itself (256^3 / 360 views 5.7 ms, 5.5 with one split; 512^3 80 ms).
+inline int adjoint_tile_splits(const int* n, int n_views) {
+  const size_t vol = (size_t)n[0] * n[1] * n[2] * sizeof(float);
+  const size_t tiles = (size_t)((n[0] + kTileEdge - 1) / kTileEdge) *
+                       ((n[1] + kTileEdge - 1) / kTileEdge) * ((n[2] + 127) / 128);
+  size_t s = (2048 + 2 * tiles - 1) / (2 * tiles);
+  const size_t by_views = n_views / 6 > 1 ? (size_t)n_views / 6 : 1;
+  const size_t by_bytes = ((size_t)256 << 20) / (2 * vol);
+  if (s > by_views) s = by_views;
+  if (s > by_bytes) s = by_bytes;
+  return (int)s;
+}
 
 // Launch configuration of the forward kernel.
 struct FwdTile {
@@ -115,8 +143,20 @@ struct ResCol {
 int launch_adjoint_value_table(const gjp_geometry* g, const double* views, const float* sino,
                                int view0, int n_chunk, float* vals, ResCol* cols, int* mask,
                                hipStream_t s);
-// Column gather from the ray table (table, cols) or, if vals is not null,
-// from the value table (vals, rcols); other geometries: tile splat (table).
+// Tile adjoint of column geometries (gjp_adjoint_tiles.hip): n_views views
+// (views, proj: the first one's entries) of rays scaled by their step lengths
+// (launch_adjoint_scale); adds to vol or overwrites it. part: scratch for 2 x
+// splits partial volumes, splits = adjoint_tile_splits; null for 0 splits.
+int launch_adjoint_scale(const gjp_geometry* g, const double* views, const float* sino, int n_views,
+                         float* out, hipStream_t s);
+int launch_adjoint_tiles(const gjp_geometry* g, const double* views, const float* proj,
+                         const float* rays, int n_views, bool accumulate, float* vol, float* part,
+                         int splits, hipStream_t s);
+// launch_adjoint_value_table without cols writes launch_adjoint_scale's rays.
+// Column gather from the ray table (table, cols) or, if vals and rcols are not
+// null, from the value table (vals, rcols); vals without rcols: the scaled rays
+// of launch_adjoint_tiles, followed (from the next multiple of 64 values) by
+// its partial volumes; other geometries: tile splat (table).
 int launch_adjoint_gather(const gjp_geometry* g, const float* proj, const float4* table,
                           const float4* cols, const float* vals, const ResCol* rcols,
                           const int* mask, int view0, int c0, int n_chunk, bool accumulate,

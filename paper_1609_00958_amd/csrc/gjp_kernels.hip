@@ -2157,6 +2157,12 @@ int launch_adjoint_value_table(const gjp_geometry* g, const double* views, const
   const long long nb = (n_rays + 255) / 256;
   if (nb > 0xffffffffll) return set_error(-4, "adjoint: view chunk too large");
   TimedLaunch t = timing_begin("adjoint_table", s);
+  if (!cols) {
+    const int st = launch_adjoint_scale(g, views + 12 * (size_t)view0,
+                                        sino + (size_t)view0 * g->n_u * g->n_v, n_chunk, vals, s);
+    timing_end("adjoint_table", t, s);
+    return st;
+  }
   adj_value_table_kernel<<<(unsigned)nb, 256, 0, s>>>(views, g->gg, sino, g->n_u, g->n_v, view0,
                                                        n_rays, vals, cols, mask);
   timing_end("adjoint_table", t, s);
@@ -2168,6 +2174,18 @@ int launch_adjoint_gather(const gjp_geometry* g, const float* proj, const float4
                           const int* mask, int view0, int c0, int n_chunk, bool accumulate,
                           float* vol, hipStream_t s) {
   TimedLaunch t = timing_begin("adjoint_gather", s);
+  if (vals && !rcols) {
+    const double* views = nullptr;
+    int st = geometry_device(g, &views, &proj);
+    const int splits = adjoint_tile_splits(g->n, n_chunk);
+    const size_t n_rays = (size_t)n_chunk * g->n_u * g->n_v;
+    float* part = splits ? const_cast<float*>(vals) + ((n_rays + 63) & ~(size_t)63) : nullptr;
+    if (st == 0)
+      st = launch_adjoint_tiles(g, views + 12 * (size_t)view0, proj + 12 * (size_t)view0, vals,
+                                n_chunk, accumulate, vol, part, splits, s);
+    timing_end("adjoint_gather", t, s);
+    return st;
+  }
   const int acc = accumulate ? 1 : 0;
   if (g->separable) {
     int nzb, nyb, ntx, nty;

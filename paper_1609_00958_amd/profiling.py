@@ -23,7 +23,7 @@ import os
 import re
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("csrc/gjp_kernels.hip", "csrc/gjp_ray.h")
+KERNEL_SOURCES = ("csrc/gjp_kernels.hip", "csrc/gjp_adjoint_tiles.hip", "csrc/gjp_ray.h")
 
 # First match wins: the longer kernel names come before their substrings.
 SHORT = (
@@ -41,6 +41,9 @@ SHORT = (
     ("fwd_kernel<gjp::bf16_t", "forward_bf16"),
     ("fwd_kernel<gjp::f16_t", "forward_f16"),
     ("adj_value_table_kernel", "adjoint_table"),
+    ("adj_scale_kernel", "adjoint_table"),
+    ("adj_tile_kernel", "adjoint_gather"),
+    ("adj_sum_kernel", "adjoint_sum"),
     ("adj_gather_sep_kernel", "adjoint_gather"),
     ("adj_splat_kernel", "adjoint_gather"),
     ("adj_table_kernel", "adjoint_table"),
