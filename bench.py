@@ -16,7 +16,7 @@ forward, 20 gradient-descent steps of the differentiable projector, one
 batched launch of the 32-instance uneven workload, the paper's speed geometry
 (Table I: ms per projection), a 1024^3 BF16/FP16 forward, a 2048^3 FP32
 forward and SART iterations on the 256^3 workload. `roofline` refers to the FP32 forward kernel and its
-binding unit (the vector-memory address path); the HBM fraction from the
+binding unit (the vector ALUs); the HBM fraction from the
 committed byte counters and the paper's access rate are reported beside it.
 
 Prints one JSON line on stdout; progress goes to stderr.
@@ -35,11 +35,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# The vector-memory address path takes a wavefront load instruction whose lanes
-# hit irregular 16-byte (or 8-/12-byte) locations at 4 lanes per clock per
-# compute unit: 256 CUs x 2.4 GHz x 4 lane addresses.
-N_CU, CLOCK_HZ, ADDR_LANES_PER_CLK = 256, 2.4e9, 4
-ADDR_PEAK = N_CU * CLOCK_HZ * ADDR_LANES_PER_CLK
+# FP32 vector lanes: 256 CUs x 4 SIMDs x 32 lanes per clock x 2.4 GHz.
+VALU_PEAK = 256 * 4 * 32 * 2.4e9
+VALU_OPS_PER_SAMPLE = 7
 # The paper's GJP_lin FP32 forward, volume in global memory (Table I, Sec.
 # IV-C geometry): ms per projection.
 PAPER_T1_MS = {"GTX 1080": 2.70, "GTX 970": 5.69}
@@ -201,22 +199,6 @@ def aux_dtypes(T, torch, gjp, G, x, S, fwd_ms, autotune):
                      "speedup_vs_f32": fwd_ms / ms}
         del xv
     return res
-
-
-def aux_one_ray(T, torch, gjp, G, x, S, fwd_ms):
-    """The FP32 forward with one ray per lane (64-wide tiles: one 16-byte load
-    per sample), then the autotuned configuration again."""
-    y = torch.empty(G.sino_shape, device=x.device)
-    cfg = gjp.get_forward_tile(G, torch.float32)
-    gjp.set_forward_tile(G, torch.float32, 64, 8, 4)
-    try:
-        gjp.forward(x, G, y)
-        r = T.run(lambda: gjp.forward(x, G, y), 3, ("forward",))
-    finally:
-        gjp.set_forward_tile(G, torch.float32, *cfg)
-    ms = r["forward"]["ms_per_launch"]
-    return {"ms": ms, "ray_samples_per_s": S / (ms * 1e-3), "launch_config": [64, 8, 4],
-            "tuned_f32_speedup": ms / fwd_ms}
 
 
 def aux_naive(T, torch, gjp, G, x, S, fwd_ms):
@@ -508,23 +490,21 @@ def main():
     log(f"FP32 forward: {step_ms:.2f} ms per step (kernel {fwd_ms:.2f} ms, pad "
         f"{r['pad']['ms_per_launch']:.2f} ms); {value:.4g} ray-samples/s")
 
-    # roofline of the FP32 forward kernel on the vector-memory address path:
-    # each irregular 16-byte load of a lane is one lane address; one per sample
-    # with one ray per lane, two per three samples with three rays per lane
-    # (192-wide tiles, where the rays of a lane share their pair elements)
+    # roofline of the FP32 forward kernel on the vector ALUs: a sample of the row
+    # forward takes seven lane operations (position, voxel, LDS address, fraction,
+    # lower weight, two FMAs) besides what its wavefront does once per plane
     tile_cfg = gjp.get_forward_tile(G, torch.float32)
-    loads_per_sample = 2.0 / 3.0 if tile_cfg[0] == 192 else 1.0
-    fwd_kernel = "forward_f32_triples" if tile_cfg[0] == 192 else "forward_f32"
-    achieved = loads_per_sample * S / (fwd_ms * 1e-3)
+    fwd_kernel = "forward_f32_rows"
+    achieved = VALU_OPS_PER_SAMPLE * S / (fwd_ms * 1e-3)
     traffic = measured_traffic(cfg.name, fwd_kernel)
     roofline = {
         "kernel": fwd_kernel,
-        "bound": "vmem_address",
+        "bound": "valu",
         "achieved": achieved,
-        "peak": ADDR_PEAK,
-        "unit": "lane addresses/s",
-        "lane_addresses_per_sample": loads_per_sample,
-        "frac": achieved / ADDR_PEAK,
+        "peak": VALU_PEAK,
+        "unit": "lane operations/s",
+        "lane_operations_per_sample": VALU_OPS_PER_SAMPLE,
+        "frac": achieved / VALU_PEAK,
         "traffic": (traffic[0] + traffic[1]) if traffic else None,
         "hbm_GBps": ((traffic[0] + traffic[1]) / (fwd_ms * 1e-3) / 1e9) if traffic else None,
         "hbm_frac": ((traffic[0] + traffic[1]) / (fwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS)
@@ -542,18 +522,11 @@ def main():
     if "adjoint" in want:
         _aux("adjoint", lambda: aux_adjoint(T, torch, gjp, G, x, S, fwd_ms), kernels)
     if "dtypes" in want:
-        _aux("forward_f32_one_ray", lambda: aux_one_ray(T, torch, gjp, G, x, S, fwd_ms), kernels)
-
         def dts():
             d = aux_dtypes(T, torch, gjp, G, x, S, fwd_ms, not args.no_autotune)
             kernels["forward_bf16"], kernels["forward_f16"] = d["bf16"], d["f16"]
-            out = {"speedup_bf16_vs_f32": d["bf16"]["speedup_vs_f32"],
-                   "speedup_f16_vs_f32": d["f16"]["speedup_vs_f32"]}
-            one = kernels.get("forward_f32_one_ray", {}).get("ms")
-            if one:
-                out["speedup_bf16_vs_f32_one_ray"] = one / d["bf16"]["ms"]
-                out["speedup_f16_vs_f32_one_ray"] = one / d["f16"]["ms"]
-            return out
+            return {"speedup_bf16_vs_f32": d["bf16"]["speedup_vs_f32"],
+                    "speedup_f16_vs_f32": d["f16"]["speedup_vs_f32"]}
         _aux("storage_speedups", dts, kernels)
     if "naive" in want:
         _aux("forward_naive_f32", lambda: aux_naive(T, torch, gjp, G, x, S, fwd_ms), kernels)

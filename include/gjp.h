@@ -95,7 +95,10 @@ gjp_status gjp_destroy_geometry(gjp_geometry *g);
    d_vol: device, n0*n1*n2 elements of `vol_dtype` (gjp_dtype), C order,
    aligned to its element size. d_sino: device, n_views*n_u*n_v floats,
    overwritten. BF16/FP16 volumes are widened to FP32 in registers; the
-   accumulation is FP32 in every case. Two zero-padded pair copies of the
+   accumulation is FP32 in every case. Column geometries (every dv parallel to
+   axis 2, no ray driven by axis 2: circular trajectories) with enough rays in a
+   column read the volume's rows in place. Otherwise, and for 16-bit rows that do
+   not start on 4 bytes, two zero-padded pair copies of the
    volume (about 4x its size) are taken from the stream-ordered pool for the
    duration of the call; if the pool cannot serve them, its cached memory is
    returned to the device (after synchronising `stream`) and the request
@@ -118,8 +121,8 @@ gjp_status gjp_forward_project(const gjp_geometry *g, const void *d_vol, int32_t
    other projection call with it on that device makes one. Calls on one device
    share the scratch, whose contents are those of the last call: calls that
    overlap on one device (different streams, or threads) race and must be
-   serialised by the caller. Calls no hipMalloc, hipFree or other allocating
-   routine. Errors: GJP_EINVAL (as gjp_forward_project; padded copies larger
+   serialised by the caller, whether or not their geometries need the copies.
+   Calls no hipMalloc, hipFree or other allocating routine. Errors: GJP_EINVAL (as gjp_forward_project; padded copies larger
    than the scratch: each is (n0+2) * (n1+2) * (n2+3 rounded down to even)
    * 2 * element size bytes rounded up to 256, and both must fit; no device
    copy of the geometry yet),
@@ -162,8 +165,9 @@ gjp_status gjp_back_project(const gjp_geometry *g, const float *d_sino, float *d
    first use for a given list of geometries and replayed afterwards. Each
    instance runs its tuned tile shape (gjp_autotune_forward /
    gjp_set_forward_tile; a two-rays-per-lane choice runs as the one-ray tile,
-   whose sums are the same); instances with three rays per lane form classes
-   of their own, one persistent launch per class. Each sinogram is bitwise
+   whose sums are the same); instances with three rays per lane, and those whose
+   rows are read in place, form classes of their own, one persistent launch per
+   class. Each sinogram is bitwise
    equal to the one gjp_forward_project produces for the same instance and
    tile shape. Arrays g, d_vols, dtypes, d_sinos are host
    arrays of length n >= 1; every d_sinos[i] holds n_views*n_u*n_v floats.
@@ -211,7 +215,8 @@ gjp_status gjp_count_samples(const gjp_geometry *g, uint64_t *out);
    file is ignored. *tile_v_out receives the chosen number of detector pixels
    along v per wavefront row (192 when three pixels per lane share their
    loads, any storage type; 128 when two do, 16-bit storage only; else 64, 32
-   or 16). Synchronises `stream`.
+   or 16; 64 for geometries whose rows are read in place, which have no ray
+   tiles: their view group only is chosen). Synchronises `stream`.
    Errors: GJP_EINVAL, GJP_ENOMEM, GJP_EHIP. */
 gjp_status gjp_autotune_forward(const gjp_geometry *g, const void *d_vol, int32_t vol_dtype,
                                 float *d_sino, void *stream, int32_t *tile_v_out);
@@ -227,7 +232,8 @@ gjp_status gjp_autotune_forward(const gjp_geometry *g, const void *d_vol, int32_
    are the same); view_group =
    consecutive views that take their turn on each ray tile together (1 to
    64); load_group = planes whose volume loads a lane issues together (2 or
-   4). tile_v = 0 removes this process's choice (the on-disk cache or the
+   4). Geometries whose rows are read in place (gjp_forward_project) use
+   view_group only. tile_v = 0 removes this process's choice (the on-disk cache or the
    default applies again; the other arguments are ignored). Not written to
    the on-disk cache. Host-only. Errors: GJP_EINVAL. */
 gjp_status gjp_set_forward_tile(const gjp_geometry *g, int32_t vol_dtype, int32_t tile_v,

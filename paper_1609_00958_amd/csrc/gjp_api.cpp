@@ -360,6 +360,65 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
   return true;
 }
 
+// Largest ray spacing along axis 2 (voxels per detector row) on the grid's
+// planes and steepest climb along axis 2 (voxels per plane) of a column
+// geometry.
+static void column_spacing(const gjp_geometry& g, double& spacing, double& climb) {
+  spacing = climb = 0.0;
+  for (int v = 0; v < g.n_views; ++v) {
+    const double* o = g.views_grid.data() + 12 * (size_t)v;
+    const double b1 = fabs(o[11]);
+    if (g.beam == GJP_PARALLEL) {
+      spacing = std::max(spacing, b1);
+      climb = std::max(climb, fabs(o[2]) / std::max(fabs(o[0]), fabs(o[1])));
+      continue;
+    }
+    for (int iu = 0; iu < g.n_u; ++iu) {
+      const double r[2] = {o[3] + (double)iu * o[6] - o[0], o[4] + (double)iu * o[7] - o[1]};
+      const int m = fabs(r[1]) > fabs(r[0]) ? 1 : 0;
+      if (r[m] == 0.0) continue;
+      const double z0 = o[5] + (double)iu * o[8] - o[2], z1 = z0 + (double)(g.n_v - 1) * o[11];
+      const double d = std::max(fabs(-1.0 - o[m]), fabs((double)g.n[m] - o[m])) / fabs(r[m]);
+      spacing = std::max(spacing, d * b1);
+      climb = std::max(climb, std::max(fabs(z0), fabs(z1)) / fabs(r[m]));
+    }
+  }
+}
+
+// Rays per lane of the row forward (gjp_forward_rows.hip), or 0 where the padded
+// copies are sampled instead: not a column geometry, rays so far apart that 128
+// of them span more than the window, or too few rays in a column to share its
+// rows. The costs are times per column and plane as measured at 256^3, 360 views
+// of 384 columns (1 = 1 ms in all): a wavefront of 64 r rays 1.81, 2.05, 2.25
+// and 3.26 for r = 2, 3, 4 and 6 (with voxels of a second load: +0.5), a
+// wavefront of the copies' kernel 0.92 per 64 rays; their two copies take 14 us
+// and 6.5 ps per voxel. 64^3, 64 x 64 rays: 22 against 31 us for 64 views, 93
+// against 64 us for 360.
+static int rows_per_lane(const gjp_geometry& g) {
+  if (!g.separable) return 0;
+  const double s0 = (double)g.n[1] * g.n[2] * 4.0, s1 = (double)g.n[2] * 4.0;
+  if (66.0 * (s0 + s1) >= 2147483648.0) return 0;  // 31-bit offsets within 64 planes
+  double b, climb;
+  column_spacing(g, b, climb);
+  int best = 0;
+  double best_cost = 1.0e300;
+  for (int r : {2, 3, 4, 6}) {
+    const double window = (64.0 * r - 1.0) * b + 31.0 * climb + 9.0;
+    if (!(window < 511.0)) break;
+    const double cost = ceil(g.n_v / (64.0 * r)) *
+                        (1.3 + 0.25 * r + (window < 253.0 ? 0.0 : window < 317.0 ? 0.5 : 0.9));
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = r;
+    }
+  }
+  const double planes = (double)std::max(g.n[0], g.n[1]) * g.n_u * g.n_views;
+  const double voxels = (double)g.n[0] * g.n[1] * g.n[2];
+  if (28.0e-12 * planes * (best_cost - 0.92 * ceil(g.n_v / 64.0)) > 14.0e-6 + 6.5e-12 * voxels)
+    return 0;
+  return best;
+}
+
 extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geometry** out) {
   if (!d || !out) return fail(GJP_EINVAL, "gjp_create_geometry: null pointer");
   *out = nullptr;
@@ -440,6 +499,7 @@ extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geomet
   }
   g->separable = columns_share_inplane_setup(*g);
   double rows[2];
+  g->rows = rows_per_lane(*g);
   g->tiles = tile_rows(*g, rows) && rows[0] <= gjp::kTileMaxRows;
   for (int k = 0; k < 2; ++k) g->tile_rows[k] = g->tiles ? (int)std::min(rows[k], 1.0e9) : 0;
   *out = g.release();
@@ -769,9 +829,16 @@ long long padded_elems(const int* n) {
   return (long long)(n[0] + 2) * (long long)(n[1] + 2) * gjp::padded_pitch(n[2]);
 }
 
-void fill_fwd_args(const gjp_geometry* g, const double* d_views, const void* padded,
-                   float* sino, const FwdTile& tile, FwdArgs& a) {
-  (void)padded;
+// Rays per lane of the row forward, or 0 where the padded copies are sampled.
+// 16-bit rows that do not all start on 4 bytes would have to be read element by
+// element: 81 us instead of 42 for FP16 97 x 83 x 121 and 45 views of 129 x 101.
+int rows_of(const gjp_geometry* g, const void* d_vol, int dtype) {
+  return dtype == GJP_F32 || (g->n[2] % 2 == 0 && (uintptr_t)d_vol % 4 == 0) ? g->rows : 0;
+}
+
+// rows: rays per lane of the row forward (rows_of), 0 for the padded copies.
+void fill_fwd_args(const gjp_geometry* g, const double* d_views, int rows, float* sino,
+                   const FwdTile& tile, FwdArgs& a) {
   const long long p2 = gjp::padded_pitch(g->n[2]), p1 = g->n[1] + 2;
   a.S1 = p2;
   a.S0 = p1 * p2;
@@ -791,6 +858,12 @@ void fill_fwd_args(const gjp_geometry* g, const double* d_views, const void* pad
   const int tile_u = gjp::tile_u_columns(tile.tile_v_log2);
   a.tiles_v = (g->n_v + tile_v - 1) / tile_v;
   a.tiles_u = (g->n_u + tile_u - 1) / tile_u;
+  a.rows = rows;
+  a.vol = nullptr;
+  if (rows) {
+    a.tiles_v = (g->n_v + 64 * rows - 1) / (64 * rows);
+    a.tiles_u = (g->n_u + 3) / 4;
+  }
   a.tiles_per_view = a.tiles_v * a.tiles_u;
 }
 
@@ -840,7 +913,12 @@ gjp_status validate_fwd(const gjp_geometry* g, const void* d_vol, int32_t dtype,
 int forward_into(const gjp_geometry* g, const double* d_views, const void* d_vol, int dtype,
                  float* d_sino, void* padded, hipStream_t s, const FwdTile& tile) {
   FwdArgs a;
-  fill_fwd_args(g, d_views, nullptr, d_sino, tile, a);
+  const int rows = rows_of(g, d_vol, dtype);
+  fill_fwd_args(g, d_views, rows, d_sino, tile, a);
+  if (rows) {
+    a.vol = d_vol;
+    return gjp::launch_forward(a, dtype, g->weight, false, g->n_views, s);
+  }
   set_padded(a, padded, dtype, g->n);
   int st = gjp::launch_pad(d_vol, const_cast<void*>(a.vol_a), const_cast<void*>(a.vol_b), dtype,
                            g->n, s);
@@ -857,6 +935,8 @@ gjp_status forward_with_tile(const gjp_geometry* g, const void* d_vol, int32_t d
   if (st != GJP_OK) return (gjp_status)st;
   if (!block_fits_32bit(g->n, dtype))
     return fail(GJP_EUNSUPPORTED, "forward: volume planes too large for 32-bit block offsets");
+  if (rows_of(g, d_vol, dtype))
+    return (gjp_status)forward_into(g, d_views, d_vol, dtype, d_sino, nullptr, s, tile);
   void* padded = nullptr;
   GJP_HIP(scratch_alloc(&padded, (size_t)(2 * copy_bytes(g->n, dtype)), s),
           "forward: padded pair copies");
@@ -944,9 +1024,10 @@ extern "C" gjp_status gjp_autotune_forward(const gjp_geometry* g, const void* d_
   // tile shape and view group with four-plane load groups, then two-plane
   // groups for the best of them
   // two rays per lane (k = 7) only for 16-bit storage; three (k = 8) for all
-  const bool pairs = vol_dtype != GJP_F32;
+  // (the row forward has no tile shapes: view groups only)
+  const bool pairs = vol_dtype != GJP_F32, rows = rows_of(g, d_vol, vol_dtype) != 0;
   for (int k : {8, 7, 6, 5, 4}) {
-    if (k == 7 && !pairs) continue;
+    if ((k == 7 && !pairs) || (k != 6 && rows)) continue;
     for (int vg : {8, 16, 1}) {
       FwdTile t;
       t.tile_v_log2 = k;
@@ -957,7 +1038,7 @@ extern "C" gjp_status gjp_autotune_forward(const gjp_geometry* g, const void* d_
     }
     if (st != GJP_OK) break;
   }
-  if (st == GJP_OK) {
+  if (st == GJP_OK && !rows) {
     FwdTile t = best;
     t.ru_group = 2;
     st = trial(t);
@@ -1183,12 +1264,13 @@ std::map<std::string, std::shared_ptr<BatchPlan>> g_plans;
 uint64_t g_plan_clock = 0;  // guarded by g_plan_mu
 constexpr size_t kMaxPlans = 8;
 
-std::string plan_key(int n, const gjp_geometry* const* g, const int32_t* dtypes, int dvc) {
+std::string plan_key(int n, const gjp_geometry* const* g, const void* const* d_vols,
+                     const int32_t* dtypes, int dvc) {
   std::string k = std::to_string(dvc);
   for (int i = 0; i < n; ++i) {
     k += "|" + std::to_string(g[i]->id) + ":" + std::to_string(dtypes[i]);
     const FwdTile t = tile_for(g[i], dtypes[i]);
-    k += ":" + std::to_string(t.tile_v_log2);
+    k += ":" + std::to_string(t.tile_v_log2) + ":" + std::to_string(rows_of(g[i], d_vols[i], dtypes[i]));
   }
   return k;
 }
@@ -1216,7 +1298,8 @@ void estimate_group_costs(const gjp_geometry* const* g, const std::vector<BatchI
       const gjp_geometry* G = g[w.inst];
       const FwdArgs& a = insts[w.inst].a;
       const int kv = a.tile_v_log2;
-      const int tile_u = gjp::tile_u_columns(kv), tile_v = gjp::tile_v_pixels(kv);
+      const int tile_u = a.rows ? 4 : gjp::tile_u_columns(kv);
+      const int tile_v = a.rows ? 64 * a.rows : gjp::tile_v_pixels(kv);
       const int tv = w.tile / a.tiles_u, tu = w.tile - tv * a.tiles_u;  // the kernels' order
       const int u_lo = tu * tile_u, v_lo = tv * tile_v;
       const int u_hi = std::min(G->n_u, u_lo + tile_u) - 1;
@@ -1244,8 +1327,8 @@ void estimate_group_costs(const gjp_geometry* const* g, const std::vector<BatchI
   }
 }
 
-gjp_status build_plan(int n, const gjp_geometry* const* g, const int32_t* dtypes, int dvc,
-                      std::shared_ptr<BatchPlan>& out) {
+gjp_status build_plan(int n, const gjp_geometry* const* g, const void* const* d_vols,
+                      const int32_t* dtypes, int dvc, std::shared_ptr<BatchPlan>& out) {
   auto P = std::make_shared<BatchPlan>();
   P->device = dvc;
   P->host.resize(n);
@@ -1257,9 +1340,10 @@ gjp_status build_plan(int n, const gjp_geometry* const* g, const int32_t* dtypes
     if (!block_fits_32bit(g[i]->n, dtypes[i]))
       return fail(GJP_EUNSUPPORTED, "batched: volume planes too large for 32-bit block offsets");
     pad_off[i] = pad_bytes;
-    pad_bytes += (size_t)(2 * copy_bytes(g[i]->n, dtypes[i]));
+    if (!rows_of(g[i], d_vols[i], dtypes[i]))
+      pad_bytes += (size_t)(2 * copy_bytes(g[i]->n, dtypes[i]));
   }
-  GJP_HIP(hipMalloc(&P->padded_all, pad_bytes), "batched: padded volumes");
+  if (pad_bytes) GJP_HIP(hipMalloc(&P->padded_all, pad_bytes), "batched: padded volumes");
   long long total_items = 0;
   for (int i = 0; i < n; ++i) {
     const double* d_views = nullptr;
@@ -1274,13 +1358,15 @@ gjp_status build_plan(int n, const gjp_geometry* const* g, const int32_t* dtypes
     // the batched launch runs the tuned tile with one or three rays per lane;
     // a tuned two-rays-per-lane tile becomes the one-ray tile (same sums)
     if (t2.tile_v_log2 == 7) t2.tile_v_log2 = 6;
-    fill_fwd_args(g[i], d_views, nullptr, nullptr, t2, I.a);
-    I.padded = static_cast<char*>(P->padded_all) + pad_off[i];
-    set_padded(I.a, I.padded, dtypes[i], g[i]->n);
+    fill_fwd_args(g[i], d_views, rows_of(g[i], d_vols[i], dtypes[i]), nullptr, t2, I.a);
+    if (!I.a.rows) {
+      I.padded = static_cast<char*>(P->padded_all) + pad_off[i];
+      set_padded(I.a, I.padded, dtypes[i], g[i]->n);
+      I.padded_elems = padded_elems(g[i]->n);
+    }
     I.n_views = g[i]->n_views;
     I.dtype = dtypes[i];
     I.weight = g[i]->weight;
-    I.padded_elems = padded_elems(g[i]->n);
     I.idx64 = needs_idx64(g[i]->n, dtypes[i]) ? 1 : 0;
     total_items += (long long)I.n_views * I.a.tiles_per_view;
   }
@@ -1324,7 +1410,9 @@ gjp_status build_plan(int n, const gjp_geometry* const* g, const int32_t* dtypes
     try {
       for (const auto& w : groups) {
         const BatchInst& I = P->host[w.inst];
-        if (gjp::batch_class(I.dtype, I.weight, I.idx64, I.a.tile_v_log2 == 8 ? 1 : 0) != c)
+        if (c != (I.a.rows ? gjp::batch_rows_class(I.dtype, I.weight)
+                           : gjp::batch_class(I.dtype, I.weight, I.idx64,
+                                              I.a.tile_v_log2 == 8 ? 1 : 0)))
           continue;
         std::vector<uint2>& dst = q[gi++ % gjp::kBatchQueues];
         const int kg = std::min(std::max(1, I.a.view_group), I.n_views - w.v0);
@@ -1368,7 +1456,7 @@ gjp_status build_plan(int n, const gjp_geometry* const* g, const int32_t* dtypes
   hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
   int st = GJP_OK;
   if (e == hipSuccess) {
-    st = gjp::launch_batched_pad(P->d_insts, n, cap);
+    if (pad_bytes) st = gjp::launch_batched_pad(P->d_insts, n, cap);
     if (st == GJP_OK)
       st = gjp::launch_zero_ints(P->d_counter, (int)P->cls.size() * gjp::kBatchQueues, cap);
     for (size_t k = 0; k < P->cls.size() && st == GJP_OK; ++k)
@@ -1419,7 +1507,7 @@ extern "C" gjp_status gjp_forward_project_batched(int32_t n, const gjp_geometry*
   hipStream_t s = (hipStream_t)stream;
   int dvc = 0;
   GJP_HIP(hipGetDevice(&dvc), "hipGetDevice");
-  const std::string key = plan_key(n, g, dtypes, dvc);
+  const std::string key = plan_key(n, g, d_vols, dtypes, dvc);
   std::shared_ptr<BatchPlan> P;
   {
     std::lock_guard<std::mutex> lk(g_plan_mu);
@@ -1430,7 +1518,7 @@ extern "C" gjp_status gjp_forward_project_batched(int32_t n, const gjp_geometry*
     }
   }
   if (!P) {
-    gjp_status st = build_plan(n, g, dtypes, dvc, P);
+    gjp_status st = build_plan(n, g, d_vols, dtypes, dvc, P);
     if (st != GJP_OK) return st;
     std::shared_ptr<BatchPlan> evicted;  // released after the lock
     std::lock_guard<std::mutex> lk(g_plan_mu);

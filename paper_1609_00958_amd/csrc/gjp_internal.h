@@ -27,6 +27,9 @@ struct gjp_geometry {
   // the rays of a detector column share their in-plane coefficients, and the
   // adjoint uses the column-form gather.
   bool separable = false;
+  // Rays per lane of the row forward (gjp_forward_rows.hip); 0: the forward
+  // runs on padded pair copies.
+  int rows = 0;
   // The adjoint runs as launch_adjoint_tiles, whose tiles of 64 and 128 voxels
   // along axis 2 need at most tile_rows[0] and tile_rows[1] detector rows.
   bool tiles = false;
@@ -108,6 +111,10 @@ struct FwdArgs {
   int tiles_v, tiles_u, tiles_per_view;
   int remap;
   int ru_group;         // planes per load group of the row-uniform loop (2 or 4)
+  // Row forward of column geometries (gjp_forward_rows.hip): rays per lane (0:
+  // not used), tiles of 64 rows rays by four columns, and the caller's volume.
+  int rows;
+  const void* vol;
 };
 
 // Device views of a geometry on the current device (uploads on first use).
@@ -125,6 +132,9 @@ int launch_sart_update(long long n, float* x, const float* bp, const float* c, f
                        int nonneg, hipStream_t s);
 int launch_forward(const FwdArgs& a, int dtype, int weight, bool idx64, int n_views,
                    hipStream_t s);
+// Row forward (gjp_forward_rows.hip; a.rows rays per lane), launched within
+// launch_forward and launch_batched_forward.
+void launch_forward_rows(const FwdArgs& a, int dtype, int weight, unsigned grid, hipStream_t s);
 int launch_forward_naive(const GridGeom& G, const double* views, const void* vol, int dtype,
                          int weight, int n_views, int n_u, int n_v, float* sino, hipStream_t s);
 int launch_adjoint_table(const gjp_geometry* g, const double* views, const float* sino,
@@ -177,7 +187,9 @@ int launch_batched_pad(const BatchInst* d_insts, int n_inst, hipStream_t s);
 inline int batch_class(int dtype, int weight, int idx64, int triple) {
   return ((dtype * 2 + weight) * 2 + idx64) * 2 + triple;
 }
-constexpr int kBatchClasses = 24;
+// ... and of the instances that the row forward takes.
+inline int batch_rows_class(int dtype, int weight) { return 24 + dtype * 2 + weight; }
+constexpr int kBatchClasses = 30;
 // Queues per class of the batched launch: one per XCD.
 constexpr int kBatchQueues = 8;
 // One class's persistent launch: items of its kBatchQueues queues, queue q =
@@ -185,6 +197,9 @@ constexpr int kBatchQueues = 8;
 int launch_batched_forward(const BatchInst* d_insts, const uint2* d_items, const int* d_qoff,
                            int* d_counters, int grid, int cls, hipStream_t s);
 int batched_grid_size(int cls);
+void launch_batched_rows(const BatchInst* d_insts, const uint2* d_items, const int* d_qoff,
+                         int* d_counters, int grid, int dtype, int weight, hipStream_t s);
+const void* batched_rows_function(int dtype, int weight);  // its kernel
 
 size_t dtype_size(int dtype);
 

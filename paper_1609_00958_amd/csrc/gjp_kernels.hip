@@ -2097,6 +2097,11 @@ int launch_forward(const FwdArgs& a, int dtype, int weight, bool idx64, int n_vi
   if (nb > 0xffffffffull) return set_error(-4, "forward: too many workgroups for one launch");
   const unsigned grid = (unsigned)nb;
   TimedLaunch t = timing_begin("forward", s);
+  if (a.rows) {
+    launch_forward_rows(a, dtype, weight, grid, s);
+    timing_end("forward", t, s);
+    return check_launch("row forward kernel");
+  }
   const int sel = dtype * 2 + weight;
   switch (sel) {
     case 0: launch_fwd_t<float, W_LINEAR>(a, idx64, grid, s); break;
@@ -2284,7 +2289,7 @@ int batched_grid_size(int cls) {
     GJP_BATCH_CLASSES(GJP_CASE)
 #undef GJP_CASE
     default:
-      return 1024;
+      return persistent_grid(batched_rows_function((cls - 24) / 2, (cls - 24) % 2));
   }
 }
 
@@ -2298,7 +2303,8 @@ int launch_batched_forward(const BatchInst* d_insts, const uint2* d_items, const
     GJP_BATCH_CLASSES(GJP_CASE)
 #undef GJP_CASE
     default:
-      return set_error(-4, "batched: unknown instance class");
+      launch_batched_rows(d_insts, d_items, d_qoff, d_counters, grid, (cls - 24) / 2,
+                          (cls - 24) % 2, s);
   }
   return check_launch("batched forward kernel");
 }

@@ -23,13 +23,18 @@ import os
 import re
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("csrc/gjp_kernels.hip", "csrc/gjp_adjoint_tiles.hip", "csrc/gjp_ray.h")
+KERNEL_SOURCES = ("csrc/gjp_kernels.hip", "csrc/gjp_adjoint_tiles.hip",
+                  "csrc/gjp_forward_rows.hip", "csrc/gjp_ray.h")
 
 # First match wins: the longer kernel names come before their substrings.
 SHORT = (
     ("naive_fwd_kernel<float", "forward_naive_f32"),
     ("naive_fwd_kernel<gjp::bf16_t", "forward_naive_bf16"),
     ("naive_fwd_kernel<gjp::f16_t", "forward_naive_f16"),
+    ("fwd_rows_kernel<float", "forward_f32_rows"),
+    ("fwd_rows_kernel<gjp::bf16_t", "forward_bf16_rows"),
+    ("fwd_rows_kernel<gjp::f16_t", "forward_f16_rows"),
+    ("batched_rows_kernel", "batched"),
     ("fwd_pair_kernel<gjp::bf16_t", "forward_bf16_pairs"),
     ("fwd_pair_kernel<gjp::f16_t", "forward_f16_pairs"),
     ("fwd_triple_kernel<float", "forward_f32_triples"),
