@@ -146,12 +146,14 @@ gjp_status gjp_forward_project_naive(const gjp_geometry *g, const void *d_vol,
    to axis 2, no ray is driven by axis 2 and the sources lie outside the grid
    (circular trajectories), tiles of voxels resample each detector column once
    per plane; column geometries with sources at or inside the grid gather per
-   voxel; otherwise voxel tiles accumulate in LDS with waves owning disjoint
+   voxel; other geometries gather per cube of voxels from the detector rectangle
+   around its image; where that has no bound (sources at or inside the grid) or
+   samples are clipped, voxel tiles accumulate in LDS with waves owning disjoint
    planes. No atomics touch the volume; the sums are deterministic. d_sino:
    device, n_views*n_u*n_v floats. d_vol: device, n0*n1*n2 floats, overwritten.
    Scratch for a chunk of views (the scaled rays, at most 2 GiB or one view, and
-   partial volumes of at most 256 MiB; per-ray tables of at most 512 MiB on the
-   other paths) is taken from the stream-ordered pool during the call (with the
+   partial volumes of at most 256 MiB; per-ray tables of at most 512 MiB, with
+   such partial volumes for the cubes, on the other paths) is taken from the stream-ordered pool during the call (with the
    same fallback as gjp_forward_project). Errors: GJP_EINVAL, GJP_ENOMEM,
    GJP_EHIP. */
 gjp_status gjp_back_project(const gjp_geometry *g, const float *d_sino, float *d_vol,

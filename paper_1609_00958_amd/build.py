@@ -13,7 +13,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libgjp.so")
-SOURCES = ["gjp_kernels.hip", "gjp_adjoint_tiles.hip", "gjp_forward_rows.hip", "gjp_api.cpp"]
+SOURCES = ["gjp_kernels.hip", "gjp_adjoint_tiles.hip", "gjp_adjoint_free.hip",
+           "gjp_forward_rows.hip", "gjp_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 

@@ -631,8 +631,13 @@ int launch_adjoint_tiles(const gjp_geometry* g, const double* views, const float
   }
   const int st = run(2 * splits);
   if (st != 0) return st;
-  const size_t nb = (a.slice + 255) / 256;
-  adj_sum_kernel<<<(unsigned)(nb < 4096 ? nb : 4096), 256, 0, s>>>(part, a.slice, 2 * splits,
+  return launch_adjoint_sum(part, a.slice, 2 * splits, accumulate, vol, s);
+}
+
+int launch_adjoint_sum(const float* part, size_t slice, int n_slices, bool accumulate, float* vol,
+                       hipStream_t s) {
+  const size_t nb = (slice + 255) / 256;
+  adj_sum_kernel<<<(unsigned)(nb < 4096 ? nb : 4096), 256, 0, s>>>(part, slice, n_slices,
                                                                   accumulate ? 1 : 0, vol);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(-3, std::string("adjoint sum kernel: ") + hipGetErrorString(e));

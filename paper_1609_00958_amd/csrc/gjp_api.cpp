@@ -385,6 +385,26 @@ static void column_spacing(const gjp_geometry& g, double& spacing, double& climb
   }
 }
 
+// General geometries whose adjoint gathers per voxel (gjp_adjoint_free.hip): every
+// view's detector projection has a positive denominator on the grid and two voxels
+// around it (the source in front of the grid), and samples are not clipped.
+static bool gathers_freely(const gjp_geometry& g) {
+  if (g.separable || g.gg.clip) return false;
+  for (int v = 0; v < g.n_views; ++v) {
+    const float* P = g.proj.data() + 12 * (size_t)v;
+    double lo = P[11], hi = P[11];
+    for (int k = 0; k < 3; ++k) {
+      const double e0 = -2.0 * P[8 + k], e1 = (g.n[k] + 1.0) * P[8 + k];
+      lo += std::min(e0, e1);
+      hi += std::max(e0, e1);
+    }
+    if (!(lo > 0.001 * hi)) return false;
+    for (int k = 0; k < 12; ++k)
+      if (!std::isfinite(P[k])) return false;
+  }
+  return true;
+}
+
 // Rays per lane of the row forward (gjp_forward_rows.hip), or 0 where the padded
 // copies are sampled instead: not a column geometry, rays so far apart that 128
 // of them span more than the window, or too few rays in a column to share its
@@ -500,6 +520,7 @@ extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geomet
   g->separable = columns_share_inplane_setup(*g);
   double rows[2];
   g->rows = rows_per_lane(*g);
+  g->free_gather = gathers_freely(*g);
   g->tiles = tile_rows(*g, rows) && rows[0] <= gjp::kTileMaxRows;
   for (int k = 0; k < 2; ++k) g->tile_rows[k] = g->tiles ? (int)std::min(rows[k], 1.0e9) : 0;
   *out = g.release();
@@ -1168,7 +1189,12 @@ extern "C" gjp_status gjp_back_project(const gjp_geometry* g, const float* d_sin
   void* table = nullptr;
   void* mask = nullptr;
   void* cols = nullptr;
-  GJP_HIP(scratch_alloc(&table, (size_t)chunk * per_view * entry, s), "back_project: table");
+  // (the general gather's partial volumes follow the table)
+  const size_t part =
+      g->free_gather ? (size_t)gjp::adjoint_free_splits(g->n, (int)chunk) * g->n[0] * g->n[1] *
+                           g->n[2] * sizeof(float)
+                     : 0;
+  GJP_HIP(scratch_alloc(&table, (size_t)chunk * per_view * entry + part, s), "back_project: table");
   hipError_t e = scratch_alloc(&mask, (size_t)chunk * sizeof(int), s);
   if (e == hipSuccess && col_entry > 0)
     e = scratch_alloc(&cols, (size_t)chunk * g->n_u * col_entry, s);

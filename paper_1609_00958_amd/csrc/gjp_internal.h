@@ -30,6 +30,7 @@ struct gjp_geometry {
   // Rays per lane of the row forward (gjp_forward_rows.hip); 0: the forward
   // runs on padded pair copies.
   int rows = 0;
+  bool free_gather = false;  // general geometry that adj_free_kernel takes
   // The adjoint runs as launch_adjoint_tiles, whose tiles of 64 and 128 voxels
   // along axis 2 need at most tile_rows[0] and tile_rows[1] detector rows.
   bool tiles = false;
@@ -84,6 +85,20 @@ inline int adjoint_tile_splits(const int* n, int n_views) {
   if (s > by_views) s = by_views;
   if (s > by_bytes) s = by_bytes;
   return (int)s;
+}
+
+// View splits of the gather of general geometries: about two rounds of workgroups
+// (four per compute unit), at least six views each, partial volumes of at most
+// 256 MiB.
+inline int adjoint_free_splits(const int* n, int n_views) {
+  const size_t vol = (size_t)n[0] * n[1] * n[2] * sizeof(float);
+  const size_t tiles = (size_t)((n[0] + 15) / 16) * ((n[1] + 15) / 16) * ((n[2] + 7) / 8);
+  size_t s = (2048 + tiles - 1) / tiles;
+  const size_t by_views = n_views / 6 > 1 ? (size_t)n_views / 6 : 1;
+  const size_t by_bytes = ((size_t)256 << 20) / vol;
+  if (s > by_views) s = by_views;
+  if (s > by_bytes) s = by_bytes;
+  return s > 1 ? (int)s : 1;
 }
 
 // Launch configuration of the forward kernel.
@@ -162,11 +177,21 @@ int launch_adjoint_scale(const gjp_geometry* g, const double* views, const float
 int launch_adjoint_tiles(const gjp_geometry* g, const double* views, const float* proj,
                          const float* rays, int n_views, bool accumulate, float* vol, float* part,
                          int splits, hipStream_t s);
+// Sum of partial volumes (slice floats each), added to vol if accumulate.
+int launch_adjoint_sum(const float* part, size_t slice, int n_slices, bool accumulate, float* vol,
+                       hipStream_t s);
+// Gather of general geometries (g->free_gather, gjp_adjoint_free.hip) from
+// adj_table_kernel's rays and axes of n_views views; proj: the first one's. part:
+// splits partial volumes, splits = adjoint_free_splits, used above 1.
+int launch_adjoint_free(const gjp_geometry* g, const float* proj, const float4* table,
+                        const int* mask, int n_views, bool accumulate, float* vol, float* part,
+                        int splits, hipStream_t s);
 // launch_adjoint_value_table without cols writes launch_adjoint_scale's rays.
 // Column gather from the ray table (table, cols) or, if vals and rcols are not
 // null, from the value table (vals, rcols); vals without rcols: the scaled rays
 // of launch_adjoint_tiles, followed (from the next multiple of 64 values) by
-// its partial volumes; other geometries: tile splat (table).
+// its partial volumes; other geometries: free gather (table, followed by its
+// partial volumes) or tile splat (table).
 int launch_adjoint_gather(const gjp_geometry* g, const float* proj, const float4* table,
                           const float4* cols, const float* vals, const ResCol* rcols,
                           const int* mask, int view0, int c0, int n_chunk, bool accumulate,

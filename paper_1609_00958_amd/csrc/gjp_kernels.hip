@@ -2216,6 +2216,15 @@ int launch_adjoint_gather(const gjp_geometry* g, const float* proj, const float4
 #undef GJP_GATHER
   } else {
     if (c0 != 0) return set_error(-4, "adjoint: the tile splat takes whole chunks");
+    if (g->free_gather) {
+      const size_t n_rays = (size_t)n_chunk * g->n_u * g->n_v;
+      const int st = launch_adjoint_free(
+          g, proj + 12 * (size_t)view0, table, mask, n_chunk, accumulate, vol,
+          reinterpret_cast<float*>(const_cast<float4*>(table) + 2 * n_rays),
+          adjoint_free_splits(g->n, n_chunk), s);
+      timing_end("adjoint_gather", t, s);
+      return st;
+    }
     dim3 grid((unsigned)((g->n[2] + ATZ - 1) / ATZ), (unsigned)((g->n[1] + ATY - 1) / ATY),
               (unsigned)((g->n[0] + ATX - 1) / ATX));
     if (g->weight == W_SPLINE)

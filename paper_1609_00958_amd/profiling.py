@@ -24,7 +24,7 @@ import re
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ("csrc/gjp_kernels.hip", "csrc/gjp_adjoint_tiles.hip",
-                  "csrc/gjp_forward_rows.hip", "csrc/gjp_ray.h")
+                  "csrc/gjp_adjoint_free.hip", "csrc/gjp_forward_rows.hip", "csrc/gjp_ray.h")
 
 # First match wins: the longer kernel names come before their substrings.
 SHORT = (
@@ -48,6 +48,7 @@ SHORT = (
     ("adj_value_table_kernel", "adjoint_table"),
     ("adj_scale_kernel", "adjoint_table"),
     ("adj_tile_kernel", "adjoint_gather"),
+    ("adj_free_kernel", "adjoint_gather"),
     ("adj_sum_kernel", "adjoint_sum"),
     ("adj_gather_sep_kernel", "adjoint_gather"),
     ("adj_splat_kernel", "adjoint_gather"),
