@@ -218,7 +218,8 @@ gjp_status gjp_count_samples(const gjp_geometry *g, uint64_t *out);
    along v per wavefront row (192 when three pixels per lane share their
    loads, any storage type; 128 when two do, 16-bit storage only; else 64, 32
    or 16; 64 for geometries whose rows are read in place, which have no ray
-   tiles: their view group only is chosen). Synchronises `stream`.
+   tiles: their view group only is chosen; 64 too for general geometries, which
+   have one configuration). Synchronises `stream`.
    Errors: GJP_EINVAL, GJP_ENOMEM, GJP_EHIP. */
 gjp_status gjp_autotune_forward(const gjp_geometry *g, const void *d_vol, int32_t vol_dtype,
                                 float *d_sino, void *stream, int32_t *tile_v_out);
@@ -235,7 +236,8 @@ gjp_status gjp_autotune_forward(const gjp_geometry *g, const void *d_vol, int32_
    consecutive views that take their turn on each ray tile together (1 to
    64); load_group = planes whose volume loads a lane issues together (2 or
    4). Geometries whose rows are read in place (gjp_forward_project) use
-   view_group only. tile_v = 0 removes this process's choice (the on-disk cache or the
+   view_group only, general geometries (not column ones) have one configuration
+   of their own, except in batched calls. tile_v = 0 removes this process's choice (the on-disk cache or the
    default applies again; the other arguments are ignored). Not written to
    the on-disk cache. Host-only. Errors: GJP_EINVAL. */
 gjp_status gjp_set_forward_tile(const gjp_geometry *g, int32_t vol_dtype, int32_t tile_v,

@@ -886,6 +886,23 @@ void fill_fwd_args(const gjp_geometry* g, const double* d_views, int rows, float
     a.tiles_u = (g->n_u + 3) / 4;
   }
   a.tiles_per_view = a.tiles_v * a.tiles_u;
+  a.spread = 0;
+}
+
+// General geometries: 16 x 16 pixels per workgroup and tiles dealt to the XCDs, the
+// whole columns if there are eight. Their views are unlike, and tiles at the
+// detector's ends miss the volume, so XCDs with whole views each ended far apart, and
+// every view read the whole copies through one L2: 120 x 136 x 112, 48 views of
+// 180 x 200 530 us with groups of eight views of 64 x 4 tiles, 397 view by view, 350
+// dealt (16 x 16 and 32 x 8 alike); 128^3, 12 views of 700^2 588 -> 181 us.
+void spread_tiles(const gjp_geometry* g, FwdArgs& a) {
+  const int k = 4;
+  a.tile_v_log2 = k;
+  a.tiles_v = (g->n_v + gjp::tile_v_pixels(k) - 1) / gjp::tile_v_pixels(k);
+  a.tiles_u = (g->n_u + gjp::tile_u_columns(k) - 1) / gjp::tile_u_columns(k);
+  a.spread = a.tiles_u >= 8 ? a.tiles_v : 1;
+  const int units = a.tiles_u * a.tiles_v / a.spread;
+  a.tiles_per_view = ((units + 7) & ~7) * a.spread;
 }
 
 // Bytes of one pair copy (two values per padded element), rounded up so that
@@ -936,6 +953,7 @@ int forward_into(const gjp_geometry* g, const double* d_views, const void* d_vol
   FwdArgs a;
   const int rows = rows_of(g, d_vol, dtype);
   fill_fwd_args(g, d_views, rows, d_sino, tile, a);
+  if (!g->separable) spread_tiles(g, a);
   if (rows) {
     a.vol = d_vol;
     return gjp::launch_forward(a, dtype, g->weight, false, g->n_views, s);
@@ -1045,11 +1063,13 @@ extern "C" gjp_status gjp_autotune_forward(const gjp_geometry* g, const void* d_
   // tile shape and view group with four-plane load groups, then two-plane
   // groups for the best of them
   // two rays per lane (k = 7) only for 16-bit storage; three (k = 8) for all
-  // (the row forward has no tile shapes: view groups only)
+  // (the row forward has no tile shapes: view groups only; general geometries have
+  // one configuration)
   const bool pairs = vol_dtype != GJP_F32, rows = rows_of(g, d_vol, vol_dtype) != 0;
   for (int k : {8, 7, 6, 5, 4}) {
     if ((k == 7 && !pairs) || (k != 6 && rows)) continue;
     for (int vg : {8, 16, 1}) {
+      if (!g->separable && (k != 6 || vg != 8)) continue;
       FwdTile t;
       t.tile_v_log2 = k;
       t.view_group = vg;
@@ -1059,7 +1079,7 @@ extern "C" gjp_status gjp_autotune_forward(const gjp_geometry* g, const void* d_
     }
     if (st != GJP_OK) break;
   }
-  if (st == GJP_OK && !rows) {
+  if (st == GJP_OK && !rows && g->separable) {
     FwdTile t = best;
     t.ru_group = 2;
     st = trial(t);

@@ -130,6 +130,11 @@ struct FwdArgs {
   // not used), tiles of 64 rows rays by four columns, and the caller's volume.
   int rows;
   const void* vol;
+  // Launch order of general geometries (0: groups of views): view by view, units
+  // of `spread` tiles (down a column of tiles, so that neighbours share lines in
+  // L2) dealt to the eight XCDs in turn, starting one XCD later in every view.
+  // tiles_per_view is rounded up to whole rounds.
+  int spread;
 };
 
 // Device views of a geometry on the current device (uploads on first use).

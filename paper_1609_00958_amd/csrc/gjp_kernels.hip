@@ -195,8 +195,8 @@ __global__ __launch_bounds__(256) void pad_kernel(const E* __restrict__ src, E* 
 // ---------------------------------------------------------------------------
 
 // Sampling loop for driving axes 0 and 1 with 32-bit offsets from copy A
-// (copy B follows it; both below 4 GiB together), two samples per iteration so
-// that two wide loads are in flight per lane. The lanes of a wavefront may
+// (copy B follows it; both below 4 GiB together), four samples per iteration so
+// that four wide loads are in flight per lane. The lanes of a wavefront may
 // differ in m, so the copy is chosen by offset, not by resource.
 template <typename T, int WF>
 __device__ __forceinline__ float fwd_loop_buf(const FwdArgs& a, const RaySetup& R) {
@@ -211,31 +211,26 @@ __device__ __forceinline__ float fwd_loop_buf(const FwdArgs& a, const RaySetup& 
   uint32_t off_m = (R.m == 0 ? 0u : (uint32_t)a.copy_bytes) + (uint32_t)(R.i0 + 1) * Sm +
                    (uint32_t)Sa + pe;
   float acc = 0.0f;
-  float fi = (float)R.i0;
-  int i = R.i0;
-  for (; i + 1 < R.i1; i += 2) {
-    int ia0, ib0, ia1, ib1;
-    float wfa0, wca0, wfb0, wcb0, wfa1, wca1, wfb1, wcb1;
-    sample_axis<WF>(fi, R.ga, R.ca, hia, ia0, wfa0, wca0);
-    sample_axis<WF>(fi, R.gb, R.cb, hib, ib0, wfb0, wcb0);
-    sample_axis<WF>(fi + 1.0f, R.ga, R.ca, hia, ia1, wfa1, wca1);
-    sample_axis<WF>(fi + 1.0f, R.gb, R.cb, hib, ib1, wfb1, wcb1);
-    const uint32_t o0 = (uint32_t)__mul24(ia0, Sa) + off_m + (uint32_t)ib0 * pe;
-    const uint32_t o1 = (uint32_t)__mul24(ia1, Sa) + off_m + Sm + (uint32_t)ib1 * pe;
-    const Quad q0 = buf_quad(rs, o0, 0, (const T*)nullptr);
-    const Quad q1 = buf_quad(rs, o1, 0, (const T*)nullptr);
-    acc = accumulate4(acc, wfa0, wca0, wfb0, wcb0, q0);
-    acc = accumulate4(acc, wfa1, wca1, wfb1, wcb1, q1);
-    fi += 2.0f;
-    off_m += 2 * Sm;
-  }
-  if (i < R.i1) {
-    int ia0, ib0;
-    float wfa0, wca0, wfb0, wcb0;
-    sample_axis<WF>(fi, R.ga, R.ca, hia, ia0, wfa0, wca0);
-    sample_axis<WF>(fi, R.gb, R.cb, hib, ib0, wfb0, wcb0);
-    const uint32_t o0 = (uint32_t)__mul24(ia0, Sa) + off_m + (uint32_t)ib0 * pe;
-    acc = accumulate4(acc, wfa0, wca0, wfb0, wcb0, buf_quad(rs, o0, 0, (const T*)nullptr));
+  // (the loads of four planes together; after the ray's last: its last again, not
+  // added)
+  for (int i = R.i0; i < R.i1; i += 4) {
+    Quad q[4];
+    float wfa[4], wca[4], wfb[4], wcb[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int d = min(k, R.i1 - 1 - i);
+      int ia, ib;
+      sample_axis<WF>((float)(i + d), R.ga, R.ca, hia, ia, wfa[k], wca[k]);
+      sample_axis<WF>((float)(i + d), R.gb, R.cb, hib, ib, wfb[k], wcb[k]);
+      const uint32_t o = (uint32_t)__mul24(ia, Sa) + off_m + (uint32_t)d * Sm + (uint32_t)ib * pe;
+      q[k] = buf_quad(rs, o, 0, (const T*)nullptr);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float sum = accumulate4(acc, wfa[k], wca[k], wfb[k], wcb[k], q[k]);
+      acc = i + k < R.i1 ? sum : acc;
+    }
+    off_m += 4 * Sm;
   }
   return acc;
 }
@@ -413,18 +408,26 @@ __device__ __forceinline__ float fwd_sum(const FwdArgs& a, const RaySetup& R) {
     const T* base = static_cast<const T*>(a.vol_a);
     const long long S0 = a.S0, S1 = a.S1;
     const float hia = a.G.hi[0], hib = a.G.hi[1];
-    float fi = (float)R.i0;
-    for (int i = R.i0; i < R.i1; ++i) {
-      int ia, ib;
-      float wfa, wca, wfb, wcb;
-      sample_axis<WF>(fi, R.ga, R.ca, hia, ia, wfa, wca);
-      sample_axis<WF>(fi, R.gb, R.cb, hib, ib, wfb, wcb);
-      const long long e = (long long)(ia + 1) * S0 + (long long)(ib + 1) * S1 + (i + 1);
-      Quad q;
-      ptr_pair(base + 2 * e, q.a0z0, q.a0z1);
-      ptr_pair(base + 2 * (e + S0), q.a1z0, q.a1z1);
-      acc = accumulate4(acc, wfa, wca, wfb, wcb, q);
-      fi += 1.0f;
+    // (the loads of four planes together; after the ray's last: its last again,
+    // not added)
+    for (int i = R.i0; i < R.i1; i += 4) {
+      Quad q[4];
+      float wfa[4], wca[4], wfb[4], wcb[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int ik = min(i + k, R.i1 - 1);
+        int ia, ib;
+        sample_axis<WF>((float)ik, R.ga, R.ca, hia, ia, wfa[k], wca[k]);
+        sample_axis<WF>((float)ik, R.gb, R.cb, hib, ib, wfb[k], wcb[k]);
+        const long long e = (long long)(ia + 1) * S0 + (long long)(ib + 1) * S1 + (ik + 1);
+        ptr_pair(base + 2 * e, q[k].a0z0, q[k].a0z1);
+        ptr_pair(base + 2 * (e + S0), q[k].a1z0, q[k].a1z1);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float sum = accumulate4(acc, wfa[k], wca[k], wfb[k], wcb[k], q[k]);
+        acc = i + k < R.i1 ? sum : acc;
+      }
     }
   }
   return acc;
@@ -1036,15 +1039,29 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, int view, int t) {
 // volume reads in L2 instead of each view streaming the volume again.
 template <typename T, int WF, bool IDX64, int GRP, int RPL>
 __device__ __forceinline__ void fwd_block(const FwdArgs& a) {
-  uint32_t b = blockIdx.x;
-  if (a.remap) b = xcd_remap(b, gridDim.x);
-  const uint32_t K = (uint32_t)a.view_group, tpv = (uint32_t)a.tiles_per_view;
-  const uint32_t grp = b / (K * tpv);
-  const uint32_t r = b - grp * K * tpv;
-  const uint32_t v0 = grp * K;
-  const uint32_t kg = min(K, (uint32_t)a.n_views - v0);  // views in this group
-  const uint32_t t = r / kg;
-  fwd_tile<T, WF, IDX64, GRP, RPL>(a, (int)(v0 + (r - t * kg)), (int)t);
+  int view, tile;
+  if (a.spread) {
+    // general geometries: see FwdArgs::spread
+    const uint32_t per_xcd = (uint32_t)a.tiles_per_view / 8, k = blockIdx.x / 8;
+    view = (int)(k / per_xcd);
+    const uint32_t r = k - (uint32_t)view * per_xcd, unit = (uint32_t)a.spread, uc = r / unit;
+    const uint32_t t = (8 * uc + (blockIdx.x + (uint32_t)view) % 8) * unit + (r - uc * unit);
+    const uint32_t tu = t / (uint32_t)a.tiles_v, tv = t - tu * (uint32_t)a.tiles_v;
+    if (tu >= (uint32_t)a.tiles_u) return;
+    tile = (int)(tv * (uint32_t)a.tiles_u + tu);
+  } else {
+    uint32_t b = blockIdx.x;
+    if (a.remap) b = xcd_remap(b, gridDim.x);
+    const uint32_t K = (uint32_t)a.view_group, tpv = (uint32_t)a.tiles_per_view;
+    const uint32_t grp = b / (K * tpv);
+    const uint32_t r = b - grp * K * tpv;
+    const uint32_t v0 = grp * K;
+    const uint32_t kg = min(K, (uint32_t)a.n_views - v0);  // views in this group
+    const uint32_t t = r / kg;
+    view = (int)(v0 + (r - t * kg));
+    tile = (int)t;
+  }
+  fwd_tile<T, WF, IDX64, GRP, RPL>(a, view, tile);
 }
 
 template <typename T, int WF, bool IDX64, int GRP>

@@ -1,0 +1,35 @@
+"""GPU: the forward of general geometries against the FP64 oracle where the dealing of
+its tiles to the XCDs and its groups of four planes can go wrong: fewer and more than
+eight columns of tiles, ragged ends, one view and several, rays of one to five samples
+on every driving axis. The bound is the stated one of an FP32 forward, relative L2
+1e-5 and every element within 1e-5 of the largest. Batched calls (another launch
+order) are bitwise equal."""
+import numpy as np
+import pytest
+
+import workloads
+from gpu_helpers import assert_parity, cuda, note
+
+pytestmark = pytest.mark.gpu
+
+TOL32 = 1e-5
+
+
+@pytest.mark.parametrize("beam", ["cone", "parallel"])
+@pytest.mark.parametrize("shape,n_views,n_u,n_v", [((20, 18, 22), 1, 5, 3), ((21, 17, 19), 9, 112, 17),
+                                                   ((15, 24, 18), 4, 113, 40), ((16, 16, 16), 11, 150, 5),
+                                                   ((5, 3, 4), 7, 33, 129), ((1, 2, 3), 12, 20, 20)])
+def test_tiles(oracle_mod, beam, shape, n_views, n_u, n_v):
+    import torch
+
+    import paper_1609_00958_amd as gjp
+    make = workloads.random_cone_views if beam == "cone" else workloads.random_parallel_views
+    G = gjp.Geometry(shape, make(41, n_views, shape, n_u, n_v), n_u, n_v, beam=beam)
+    og = oracle_mod.Geometry(G.shape, G.views, n_u, n_v,
+                             beam=oracle_mod.CONE if beam == "cone" else oracle_mod.PARALLEL)
+    x = np.random.default_rng(42).uniform(0, 1, size=shape).astype(np.float32)
+    note(f"general forward {beam} {shape} {n_views} x {n_u} x {n_v}")
+    d = torch.from_numpy(x).to(cuda())
+    y = gjp.forward(d, G)
+    assert_parity(y.cpu().numpy(), oracle_mod.forward(og, x), TOL32)
+    assert torch.equal(gjp.forward_batched([d], [G])[0], y)
