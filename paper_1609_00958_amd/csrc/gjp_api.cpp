@@ -1159,13 +1159,19 @@ static gjp_status back_project_tiles(const gjp_geometry* g, const double* d_view
                                      const float* d_proj, const float* d_sino, float* d_vol,
                                      hipStream_t s) {
   const size_t per_view = (size_t)g->n_u * (size_t)g->n_v * sizeof(float);
-  const long long chunk =
+  long long chunk =
       std::min<long long>(g->n_views, std::max<long long>(1, (long long)(kTileScratch / per_view)));
   const size_t vol = (size_t)g->n[0] * g->n[1] * g->n[2] * sizeof(float);
-  const int splits = gjp::adjoint_tile_splits(g->n, (int)chunk);
-  const size_t bytes = (((size_t)chunk * per_view + 255) & ~(size_t)255) + 2 * splits * vol;
   void* rays = nullptr;
-  GJP_HIP(scratch_alloc(&rays, bytes, s), "back_project: scaled rays");
+  for (;;) {  // fewer views at a time where the device has no room for their rays
+    const int splits = gjp::adjoint_tile_splits(g->n, (int)chunk);
+    const size_t bytes = (((size_t)chunk * per_view + 255) & ~(size_t)255) + 2 * splits * vol;
+    const hipError_t e = scratch_alloc(&rays, bytes, s);
+    if (e == hipSuccess) break;
+    if (e != hipErrorOutOfMemory || chunk == 1) return hip_fail(e, "back_project: scaled rays");
+    (void)hipGetLastError();
+    chunk = (chunk + 3) / 4;
+  }
   int st = GJP_OK;
   for (int v0 = 0; v0 < g->n_views && st == GJP_OK; v0 += (int)chunk) {
     const int nc = (int)std::min<long long>(chunk, g->n_views - v0);
