@@ -360,9 +360,8 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
   return true;
 }
 
-// Largest ray spacing along axis 2 (voxels per detector row) on the grid's
-// planes and steepest climb along axis 2 (voxels per plane) of a column
-// geometry.
+// Bounds of the ray spacing along axis 2 (voxels per detector row) on the grid's
+// planes and of the climb along axis 2 (voxels per plane) of a column geometry.
 static void column_spacing(const gjp_geometry& g, double& spacing, double& climb) {
   spacing = climb = 0.0;
   for (int v = 0; v < g.n_views; ++v) {
@@ -373,15 +372,24 @@ static void column_spacing(const gjp_geometry& g, double& spacing, double& climb
       climb = std::max(climb, fabs(o[2]) / std::max(fabs(o[0]), fabs(o[1])));
       continue;
     }
+    // the steepest column and the farthest plane of the axes that drive one (a bound:
+    // no division per column)
+    double r_min = 1.0e300;
+    bool used[2] = {false, false};
     for (int iu = 0; iu < g.n_u; ++iu) {
-      const double r[2] = {o[3] + (double)iu * o[6] - o[0], o[4] + (double)iu * o[7] - o[1]};
-      const int m = fabs(r[1]) > fabs(r[0]) ? 1 : 0;
-      if (r[m] == 0.0) continue;
-      const double z0 = o[5] + (double)iu * o[8] - o[2], z1 = z0 + (double)(g.n_v - 1) * o[11];
-      const double d = std::max(fabs(-1.0 - o[m]), fabs((double)g.n[m] - o[m])) / fabs(r[m]);
-      spacing = std::max(spacing, d * b1);
-      climb = std::max(climb, std::max(fabs(z0), fabs(z1)) / fabs(r[m]));
+      const double r0 = fabs(o[3] + (double)iu * o[6] - o[0]);
+      const double r1 = fabs(o[4] + (double)iu * o[7] - o[1]);
+      used[r1 > r0] = true;
+      if (r0 > 0.0 || r1 > 0.0) r_min = std::min(r_min, std::max(r0, r1));
     }
+    double d = 0.0;
+    for (int m = 0; m < 2; ++m)
+      if (used[m]) d = std::max(d, std::max(fabs(-1.0 - o[m]), fabs((double)g.n[m] - o[m])));
+    const double z0 = o[5] - o[2], z1 = z0 + (double)(g.n_u - 1) * o[8];
+    const double zv = (double)(g.n_v - 1) * o[11];
+    const double z = std::max(std::max(fabs(z0), fabs(z1)), std::max(fabs(z0 + zv), fabs(z1 + zv)));
+    spacing = std::max(spacing, d * b1 / r_min);
+    climb = std::max(climb, z / r_min);
   }
 }
 
