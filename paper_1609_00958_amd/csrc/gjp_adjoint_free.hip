@@ -120,7 +120,8 @@ __device__ __forceinline__ void gather_axis(const FreeArgs& a, const float4* T, 
         const int iu = wu0 + q + ku, iv = wv0 + r + kv;
         float4 line = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         float val = 0.0f;
-        if (iu >= 0 && iu < a.n_u && iv >= 0 && iv < a.n_v) {
+        // (always; without the test 22.6 instead of 21.6 ms for 60^3, 8 views of 1500^2)
+        if (iu < a.n_u && iv < a.n_v) {
           const float4* e = T + 2 * ((size_t)iu * a.n_v + iv);
           const float4 e0 = e[0];
           const float2 e1 = *reinterpret_cast<const float2*>(e + 1);
@@ -221,19 +222,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void a
       const float dx = m == 0 ? 0.5f : 1.5f, dy = m == 1 ? 0.5f : 1.5f, dz = m == 2 ? 0.5f : 1.5f;
       const float hu = uniform(half_extent(P, P + 8, ulo, uhi, dx, dy, dz, inv_wmin));
       const float hv = uniform(half_extent(P + 4, P + 8, vlo, vhi, dx, dy, dz, inv_wmin));
-      // integers of an interval of 2 h, at most
-      const int nu = __builtin_amdgcn_readfirstlane((int)fminf(2.0f * hu, (float)a.n_u)) + 1;
-      const int nv = __builtin_amdgcn_readfirstlane((int)fminf(2.0f * hv, (float)a.n_v)) + 1;
-      // first rays of a lane and of all lanes (beside the detector: empty entries;
-      // boxes that miss it altogether lie just beside it)
       const float fu = (float)a.n_u, fv = (float)a.n_v;
-      const int wu0 = __builtin_amdgcn_readfirstlane((int)fminf(fmaxf(ceilf(ulo - hu - 0.01f), -(float)nu), fu));
-      const int wv0 = __builtin_amdgcn_readfirstlane((int)fminf(fmaxf(ceilf(vlo - hv - 0.01f), -(float)nv), fv));
-      const int wu1 = __builtin_amdgcn_readfirstlane((int)fminf(fmaxf(ceilf(uhi - hu + 0.01f), -(float)nu), fu)) + nu;
-      const int wv1 = __builtin_amdgcn_readfirstlane((int)fminf(fmaxf(ceilf(vhi - hv + 0.01f), -(float)nv), fv)) + nv;
-      const int u0 = min(max((int)fminf(fmaxf(ceilf(uc - hu), -(float)nu), fu), wu0), wu1 - nu);
-      const int v0 = min(max((int)fminf(fmaxf(ceilf(vc - hv), -(float)nv), fv), wv0), wv1 - nv);
-      if (wu1 <= 0 || wv1 <= 0 || wu0 >= a.n_u || wv0 >= a.n_v) continue;
+      // boxes that miss the detector altogether
+      if (uhi + hu < -0.01f || vhi + hv < -0.01f || ulo - hu > fu - 0.99f || vlo - hv > fv - 0.99f)
+        continue;
+      // rays per lane: the integers of an interval of 2 h at most, and all of the
+      // detector's where it is no longer than that
+      const int nu = min(__builtin_amdgcn_readfirstlane((int)fminf(2.0f * hu, fu)) + 1, a.n_u);
+      const int nv = min(__builtin_amdgcn_readfirstlane((int)fminf(2.0f * hv, fv)) + 1, a.n_v);
+      // first rays of a lane and of all lanes. An interval that begins before the
+      // detector, or has fewer than its count left on it, is moved onto it: what it
+      // has there stays inside.
+      const auto first = [](float x, int n, int count) {
+        return min((int)fminf(fmaxf(ceilf(x), 0.0f), 1.0e9f), n - count);
+      };
+      const int wu0 = __builtin_amdgcn_readfirstlane(first(ulo - hu - 0.01f, a.n_u, nu));
+      const int wv0 = __builtin_amdgcn_readfirstlane(first(vlo - hv - 0.01f, a.n_v, nv));
+      const int wu1 = max(__builtin_amdgcn_readfirstlane(first(uhi - hu + 0.01f, a.n_u, nu)), wu0) + nu;
+      const int wv1 = max(__builtin_amdgcn_readfirstlane(first(vhi - hv + 0.01f, a.n_v, nv)), wv0) + nv;
+      const int u0 = min(max(first(uc - hu, a.n_u, nu), wu0), wu1 - nu);
+      const int v0 = min(max(first(vc - hv, a.n_v, nv), wv0), wv1 - nv);
       if (m == 0)
         gather_axis<WF, 0>(a, rays, o, wu0, wv0, wu1 - wu0, wv1 - wv0, nu, nv, u0, v0, cx, cy, cz,
                            sh, acc);
