@@ -30,6 +30,7 @@
 
 #include "gjp.h"
 #include "gjp_internal.h"
+#include "gjp_windows.h"
 
 using gjp::BatchInst;
 using gjp::FwdArgs;
@@ -361,7 +362,8 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
 }
 
 // Bounds of the ray spacing along axis 2 (voxels per detector row) on the grid's
-// planes and of the climb along axis 2 (voxels per plane) of a column geometry.
+// planes and those past them that the row forward's last step takes, and of the climb
+// along axis 2 (voxels per plane) of a column geometry.
 static void column_spacing(const gjp_geometry& g, double& spacing, double& climb) {
   spacing = climb = 0.0;
   for (int v = 0; v < g.n_views; ++v) {
@@ -384,7 +386,8 @@ static void column_spacing(const gjp_geometry& g, double& spacing, double& climb
     }
     double d = 0.0;
     for (int m = 0; m < 2; ++m)
-      if (used[m]) d = std::max(d, std::max(fabs(-1.0 - o[m]), fabs((double)g.n[m] - o[m])));
+      if (used[m])
+        d = std::max(d, std::max(fabs(-1.0 - o[m]), fabs((double)(g.n[m] - 1 + gjp::kRowStep) - o[m])));
     const double z0 = o[5] - o[2], z1 = z0 + (double)(g.n_u - 1) * o[8];
     const double zv = (double)(g.n_v - 1) * o[11];
     const double z = std::max(std::max(fabs(z0), fabs(z1)), std::max(fabs(z0 + zv), fabs(z1 + zv)));
@@ -431,8 +434,9 @@ static int rows_per_lane(const gjp_geometry& g) {
   int best = 0;
   double best_cost = 1.0e300;
   for (int r : {2, 3, 4, 6}) {
-    const double window = (64.0 * r - 1.0) * b + 31.0 * climb + 9.0;
-    if (!(window < 511.0)) break;
+    // (9: RowWindow's rounding at both ends and to groups of four)
+    const double window = (64.0 * r - 1.0) * b + (gjp::kRowPlanes - 1.0) * climb + 9.0;
+    if (!(window < gjp::kRowEntries - 1.0)) break;
     const double cost = ceil(g.n_v / (64.0 * r)) *
                         (1.3 + 0.25 * r + (window < 253.0 ? 0.0 : window < 317.0 ? 0.5 : 0.9));
     if (cost < best_cost) {

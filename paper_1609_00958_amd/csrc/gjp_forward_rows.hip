@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "gjp_internal.h"
+#include "gjp_windows.h"
 
 namespace gjp {
 
@@ -44,10 +45,8 @@ struct f16_t {
 
 namespace {
 
-// Planes that share a window of voxels along axis 2 (16: 2% slower at 512^3; a
-// longer block widens the windows of steep rays).
-constexpr int kSub = 32;
-constexpr int kRow = 512;  // a combined row in LDS: voxels, and zeros beside the grid
+constexpr int kSub = kRowPlanes;
+constexpr int kRow = kRowEntries;  // a combined row in LDS: voxels, and zeros beside the grid
 // How a window's voxels are read: a piece of 256, four voxels per lane; the same
 // and one more voxel per lane (384 rays at magnification 1.5 span up to 290); two
 // such pieces.
@@ -58,6 +57,8 @@ enum Window { ONE_PIECE, AND_TAIL, TWO_PIECES };
 constexpr int planes_together(int window, int rpl) {
   return window == ONE_PIECE && rpl < 6 ? 2 : 1;
 }
+static_assert(kRowStep % (2 * planes_together(ONE_PIECE, 2)) == 0 && kRowStep % 2 == 0,
+              "row_planes covers the planes that the loop takes");
 constexpr uint32_t kNoLower = 0x80000000u, kNoUpper = 1u;  // offsets are even and below 2^31
 
 // Four neighbouring elements of a row; 16-bit rows start on 4 bytes.
@@ -323,24 +324,16 @@ __device__ __forceinline__ void project_column(const FwdArgs& a, const void* vol
       const uint32_t size = (uint32_t)min((int64_t)total - org, (int64_t)0x7fffffff);
       const int cnt = min(64, i_hi - base);
       for (int j = 0; j < cnt; j += kSub) {
-        // window of voxels that the rays span on planes j .. j + kSub - 1: their
-        // coordinates are linear in the ray and in the plane
-        const double t0 = (double)(base + j) - sm, t1 = t0 + (double)(kSub - 1);
-        const double kl = (double)last;
-        const double c00 = A + t0 * C, c01 = A + t1 * C;
-        const double c10 = c00 + kl * (B + t0 * D), c11 = c01 + kl * (B + t1 * D);
-        const double zmin = fmin(fmin(c00, c01), fmin(c10, c11));
-        const double zmax = fmax(fmax(c00, c01), fmax(c10, c11));
-        if (!(zmax > -1.0 && zmin < (double)n2)) continue;
-        // entries lo .. hi are read; those on the grid are loaded, from a voxel on
-        // that leaves a multiple of four to the row's end (or is its first)
-        const int lo = __builtin_amdgcn_readfirstlane((int)floor(zmin - 0.01));
-        const int hi = __builtin_amdgcn_readfirstlane((int)floor(zmax + 0.01)) + 1;
-        const int first = max(lo, 0);
-        const int zd = max(first - ((first - n2) & 3), 0);
-        const int need = min(hi, n2 - 1) - zd + 1;
-        const int pad = max(zd - lo + 3, 0) & ~3;
-        if (lo < 0 || hi >= n2) {  // beside the grid: zeros
+        // window of voxels that the rays span on the planes that the loop takes (up to
+        // three past the last one's, whose rows read as zeros)
+        const int np = min(kSub, cnt - j);
+        const double t0 = (double)(base + j) - sm;
+        RowWindow win;
+        if (!row_window(A, B, C, D, t0, row_planes(np), last, n2, win)) continue;
+        const int zd = __builtin_amdgcn_readfirstlane(win.zd);
+        const int need = __builtin_amdgcn_readfirstlane(win.need);
+        const int pad = __builtin_amdgcn_readfirstlane(win.pad);
+        if (win.border) {  // beside the grid: zeros
 #pragma unroll
           for (int k = 0; k < 2 * kRow / 256; ++k)
             reinterpret_cast<f4l*>(sh.row)[64 * k + lane] = f4l{0.0f, 0.0f, 0.0f, 0.0f};
@@ -353,7 +346,6 @@ __device__ __forceinline__ void project_column(const FwdArgs& a, const void* vol
           gb[r] = (float)g;
           cb[r] = (float)(A + k * B + t0 * g - (double)zd);
         }
-        const int np = min(kSub, cnt - j);
         if (need <= 256)
           project_planes<T, WF, RPL, ONE_PIECE>(vol, size, zd, need, pad, n2, (uint32_t)Sa,
                                                  off, j, np, sh, lane, gb, cb, acc);

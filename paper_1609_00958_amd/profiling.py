@@ -24,7 +24,8 @@ import re
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ("csrc/gjp_kernels.hip", "csrc/gjp_adjoint_tiles.hip",
-                  "csrc/gjp_adjoint_free.hip", "csrc/gjp_forward_rows.hip", "csrc/gjp_ray.h")
+                  "csrc/gjp_adjoint_free.hip", "csrc/gjp_forward_rows.hip", "csrc/gjp_ray.h",
+                  "csrc/gjp_windows.h")
 
 # First match wins: the longer kernel names come before their substrings.
 SHORT = (

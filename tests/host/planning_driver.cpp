@@ -1,0 +1,188 @@
+// Driver of the library's host rules (built by tests/test_host_planning_cpu.py from
+// csrc/gjp_api.cpp for the host only): which kernel a geometry is sent to, and whether
+// what that kernel copies to LDS fits for every geometry that is sent to it. The
+// kernels' launchers are stand-ins.
+#include <math.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "gjp.h"
+#include "gjp_internal.h"
+#include "gjp_windows.h"
+
+namespace gjp {
+int launch_pad(const void*, void*, void*, int, const int*, hipStream_t) { return 0; }
+int launch_zero_ints(int*, int, hipStream_t) { return 0; }
+int launch_sart_residual(long long, const float*, const float*, const float*, float*,
+                         hipStream_t) { return 0; }
+int launch_sart_update(long long, float*, const float*, const float*, float, int, hipStream_t) {
+  return 0;
+}
+int launch_forward(const FwdArgs&, int, int, bool, int, hipStream_t) { return 0; }
+int launch_forward_naive(const GridGeom&, const double*, const void*, int, int, int, int, int,
+                         float*, hipStream_t) { return 0; }
+int launch_adjoint_table(const gjp_geometry*, const double*, const float*, int, int, float4*,
+                         float4*, int*, hipStream_t) { return 0; }
+int launch_adjoint_gather(const gjp_geometry*, const float*, const float4*, const float4*,
+                          const float*, const ResCol*, const int*, int, int, int, bool, float*,
+                          hipStream_t) { return 0; }
+int launch_adjoint_value_table(const gjp_geometry*, const double*, const float*, int, int, float*,
+                               ResCol*, int*, hipStream_t) { return 0; }
+int launch_batched_pad(const BatchInst*, int, hipStream_t) { return 0; }
+int launch_batched_forward(const BatchInst*, const uint2*, const int*, int*, int, int,
+                           hipStream_t) { return 0; }
+int batched_grid_size(int) { return 1; }
+size_t dtype_size(int dtype) { return dtype == 0 ? 4 : 2; }
+int noalloc_scratch(void**) { return -1; }
+}  // namespace gjp
+
+static int bad = 0;
+#define CHECK(c)                                                   \
+  do {                                                             \
+    if (!(c)) {                                                    \
+      if (bad < 20) fprintf(stderr, "line %d: %s\n", __LINE__, #c); \
+      ++bad;                                                       \
+    }                                                              \
+  } while (0)
+
+static uint64_t g_state = 88172645463325252ull;
+static double uniform(double a, double b) {
+  g_state ^= g_state << 13;
+  g_state ^= g_state >> 7;
+  g_state ^= g_state << 17;
+  return a + (b - a) * ((double)(g_state >> 11) / 9007199254740992.0);
+}
+static double loguniform(double a, double b) { return exp(uniform(log(a), log(b))); }
+static int integer(double a, double b) { return (int)floor(loguniform(a, b + 0.999)); }
+
+static gjp_geometry* make(const int* n, int beam, int n_views, int n_u, int n_v,
+                          const double* views) {
+  gjp_geometry_desc d;
+  memset(&d, 0, sizeof(d));
+  for (int k = 0; k < 3; ++k) {
+    d.vol_shape[k] = n[k];
+    d.voxel_size[k] = 1.0;
+  }
+  d.n_views = n_views;
+  d.n_u = n_u;
+  d.n_v = n_v;
+  d.beam = beam;
+  d.views = views;
+  gjp_geometry* g = nullptr;
+  return gjp_create_geometry(&d, &g) == GJP_OK ? g : nullptr;
+}
+
+// A column geometry's view: source `dist` from the centre at angle th and height zs (cone;
+// parallel: climb zs per unit), detector `len` away, pitches pu and pv, rows shifted by
+// `v_off` pixels, columns climbing su along axis 2.
+static void column_view(int beam, double th, double dist, double zs, double len, double pu,
+                        double pv, double su, int n_u, int n_v, double v_off, double* o) {
+  const double c = cos(th), s = sin(th);
+  const double du[3] = {-pu * s, pu * c, su}, dv[3] = {0.0, 0.0, pv};
+  const double first[3] = {beam == GJP_CONE ? dist * c : -c, beam == GJP_CONE ? dist * s : -s, zs};
+  const double mid[3] = {(dist - len) * c, (dist - len) * s, v_off * pv};
+  for (int k = 0; k < 3; ++k) {
+    o[k] = first[k];
+    o[3 + k] = (beam == GJP_CONE ? mid[k] : 0.0) - 0.5 * (n_u - 1) * du[k] -
+               0.5 * (n_v - 1) * dv[k] + (k == 2 && beam != GJP_CONE ? mid[2] : 0.0);
+    o[6 + k] = du[k];
+    o[9 + k] = dv[k];
+  }
+}
+
+// Every window of the row forward lies in its LDS row, on every plane that the sampling
+// loop takes.
+static void check_row_windows(const gjp_geometry& g) {
+  const int R = g.rows;
+  for (int view = 0; view < g.n_views; ++view) {
+    const double* v = g.views_grid.data() + 12 * (size_t)view;
+    const bool cone = g.beam == GJP_CONE;
+    for (int u = 0; u < g.n_u; ++u) {
+      const double d0 = v[3] + u * v[6], d1 = v[4] + u * v[7], d2 = v[5] + u * v[8];
+      const double s0 = cone ? v[0] : d0, s1 = cone ? v[1] : d1;
+      const double r0 = cone ? d0 - v[0] : v[0], r1 = cone ? d1 - v[1] : v[1];
+      const bool m1 = fabs(r1) > fabs(r0);
+      const double sm = m1 ? s1 : s0, rm = m1 ? r1 : r0;
+      const int nm = m1 ? g.n[1] : g.n[0];
+      if (rm == 0.0) continue;
+      for (int v0 = 0; v0 < g.n_v; v0 += 64 * R) {
+        const int last = std::min(g.n_v - v0, 64 * R) - 1;
+        const double irm = 1.0 / rm;
+        const double A = cone ? v[2] : d2 + v0 * v[11], B = cone ? 0.0 : v[11];
+        const double C = (cone ? d2 + v0 * v[11] - v[2] : v[2]) * irm, D = cone ? v[11] * irm : 0.0;
+        // blocks may begin at any plane and hold up to kRowPlanes of the grid's
+        for (int p0 = 0; p0 < nm; p0 += std::max(1, nm / 7)) {
+          const int np = std::min(gjp::kRowPlanes, nm - p0);
+          const double t0 = p0 - sm;
+          gjp::RowWindow w;
+          if (!gjp::row_window(A, B, C, D, t0, gjp::row_planes(np), last, g.n[2], w)) continue;
+          CHECK(w.pad % 4 == 0 && w.zd >= 0 && w.need >= 1);
+          CHECK(w.zd + w.need <= g.n[2]);
+          CHECK(w.pad + ((w.need + 3) & ~3) <= gjp::kRowEntries);
+          for (int i = 0; i < gjp::row_planes(np); ++i)
+            for (int k = 0; k <= last; k += std::max(1, last)) {
+              const double e = floor(A + k * B + (t0 + i) * (C + k * D)) - w.zd + w.pad;
+              CHECK(e >= 0 && e + 1 < gjp::kRowEntries);
+            }
+        }
+      }
+    }
+  }
+}
+
+static int rows_main() {
+  int taken = 0, wide = 0;
+  for (int trial = 0; trial < 4000; ++trial) {
+    const int n[3] = {integer(1, 40), integer(1, 40), integer(2, 300)};
+    const int beam = trial % 3 == 0 ? GJP_PARALLEL : GJP_CONE, n_v = integer(2, 600), n_u = 5;
+    const double reach = 0.5 * std::max(n[0], n[1]);
+    const double dist = reach + loguniform(2.0, 400.0), len = dist * uniform(1.05, 3.0);
+    const double climb = uniform(-0.99, 0.99);
+    double views[24];
+    for (int k = 0; k < 2; ++k)
+      column_view(beam, uniform(0.0, 6.28), dist,
+                  beam == GJP_CONE ? climb * dist * uniform(0.0, 1.0) : climb * 0.7, len,
+                  loguniform(0.2, 3.0), loguniform(0.05, 6.0) * (trial & 1 ? 1 : -1), 0.0, n_u, n_v,
+                  uniform(-0.5, 0.5) * n_v, views + 12 * k);
+    gjp_geometry* g = make(n, beam, 2, n_u, n_v, views);
+    CHECK(g != nullptr);
+    if (g->rows) {
+      ++taken;
+      check_row_windows(*g);
+    }
+    gjp_destroy_geometry(g);
+  }
+  // a thin volume seen steeply from below: windows that the planes past the grid widen
+  {
+    const int n[3] = {4, 4, 240};
+    double v[12];
+    for (double pv = 3.0; pv < 3.8; pv += 0.002) {
+      for (double z = -240.0; z < 0.0; z += 8.0) {
+        column_view(GJP_CONE, M_PI, 238.0, z, 476.0, 1.0, pv, 0.0, 1, 256, 0.0, v);
+        gjp_geometry* g = make(n, GJP_CONE, 1, 1, 256, v);
+        if (g->rows) {
+          ++wide;
+          check_row_windows(*g);
+        }
+        gjp_destroy_geometry(g);
+      }
+    }
+  }
+  CHECK(taken > 400 && wide > 1000);
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  const char* what = argc > 1 ? argv[1] : "";
+  if (!strcmp(what, "rows")) rows_main();
+  else {
+    fprintf(stderr, "unknown part %s\n", what);
+    return 2;
+  }
+  printf(bad ? "planning driver %s: FAILED (%d)\n" : "planning driver %s: ok\n", what, bad);
+  return bad != 0;
+}

@@ -144,3 +144,15 @@ def test_batch_equals_single_calls(gjp):
     for _ in range(2):
         for y, g, x in zip(gjp.forward_batched(vols, geoms), geoms, vols):
             assert torch.equal(y, gjp.forward(x, g))
+
+
+@pytest.mark.parametrize("z", [-178.5, -120.0, 178.5])
+@pytest.mark.parametrize("pitch_v", [3.5, 3.55, 3.6])
+def test_thin_volumes_seen_steeply(gjp, oracle_mod, pitch_v, z):
+    """Four planes, rays that climb nearly a voxel per plane from far below or above:
+    windows whose lower part lies beside the grid, at the limit of the rule."""
+    shape, n_v = (4, 4, 240), 256
+    v = gjp.views_circular_cone(2, 238.0, 476.0, 1.0, pitch_v, 3, n_v)[1:].copy()
+    v[:, 2] = z
+    G = gjp.Geometry(shape, v, 3, n_v, beam="cone")
+    _check(gjp, oracle_mod, G, 27, f"thin volume, source at height {z}, pitch {pitch_v}")

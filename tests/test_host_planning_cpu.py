@@ -1,0 +1,38 @@
+"""The library's host rules on the CPU: every geometry that a rule sends to a kernel has
+windows that fit that kernel's LDS arrays. csrc/gjp_api.cpp is compiled for the host and
+driven by tests/host/planning_driver.cpp, over random geometries and the ones at a rule's
+edge."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests", "host")
+CSRC = os.path.join(ROOT, "paper_1609_00958_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+def _run(cmd):
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, " ".join(cmd) + "\n" + r.stdout[-3000:] + r.stderr[-3000:]
+    return r.stdout
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("no hipcc")
+    out = tmp_path_factory.mktemp("planning")
+    objs = []
+    for src in (os.path.join(CSRC, "gjp_api.cpp"), os.path.join(HERE, "planning_driver.cpp")):
+        objs.append(str(out / (os.path.basename(src) + ".o")))
+        _run([HIPCC, "-x", "hip", "--cuda-host-only", "-O2", "-std=c++17", "-ffp-contract=off",
+              "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", src, "-o", objs[-1]])
+    exe = str(out / "driver")
+    _run([HIPCC, *objs, "-o", exe])
+    return exe
+
+
+def test_windows_of_the_row_forward_fit(driver):
+    assert "rows: ok" in _run([driver, "rows"])
