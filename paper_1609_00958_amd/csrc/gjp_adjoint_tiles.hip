@@ -123,31 +123,6 @@ __device__ __forceinline__ float tent(float r) {
   }
 }
 
-// In-plane part of a column's rays: origin s, direction r on axes 0 and 1 (the
-// arithmetic of ray_line, in which dv_0 = dv_1 = 0 adds nothing) and the
-// driving axis.
-struct Column {
-  double s0, s1, r0, r1;
-  int m;
-};
-__device__ __forceinline__ Column column_line(const double* __restrict__ v, bool cone, double u) {
-  Column c;
-  const double d0 = v[3] + u * v[6], d1 = v[4] + u * v[7];
-  if (cone) {
-    c.s0 = v[0];
-    c.s1 = v[1];
-    c.r0 = d0 - v[0];
-    c.r1 = d1 - v[1];
-  } else {
-    c.s0 = d0;
-    c.s1 = d1;
-    c.r0 = v[0];
-    c.r1 = v[1];
-  }
-  c.m = fabs(c.r1) > fabs(c.r0) ? 1 : 0;
-  return c;
-}
-
 // Columns of the staged chunk: the in-plane line p_a(i) = sa + (i - sm) ga of
 // a column's rays and their axis-2 coordinates a0 + t a1 + v B (t = (i - sm)
 // irm, v counted from the window's first row; irm = 0: not driven by the
@@ -243,53 +218,20 @@ __global__ __launch_bounds__(P * 64) __attribute__((amdgpu_waves_per_eu(8))) voi
     __syncthreads();  // the previous batch's windows have been read, its sums stored
     if (pl == 0) {
       const int lane = here(tid), z0 = here_u(zt), ra0 = here_u(tr) * R;
-      // windows of the slice's views batch .. batch + kViews - 1, one per lane:
-      // columns whose in-plane line can come within a voxel of the tile on its
-      // planes, rows within a voxel of it along axis 2
+      // windows of the slice's views batch .. batch + kViews - 1, one per lane
       const int gi = batch + lane;
       const int c = min(gi, ngv - 1) * a.splits + sv0;
-      const float* Q = a.proj + 12 * (size_t)c;
-      float umin = 3.0e38f, umax = -3.0e38f;
-#pragma unroll 1
-      for (int k = 0; k < 4; ++k) {
-        const float fp = (float)((k & 1) ? pm0 + P - 1 : pm0);
-        const float fr = (k & 2) ? (float)(ra0 + R) + 0.01f : (float)ra0 - 1.01f;
-        const float qx = m == 0 ? fp : fr, qy = m == 0 ? fr : fp;
-        const float un = __builtin_fmaf(Q[0], qx, __builtin_fmaf(Q[1], qy, Q[3]));
-        const float w = __builtin_fmaf(Q[8], qx, __builtin_fmaf(Q[9], qy, Q[11]));
-        const float uu = un / w;
-        umin = fminf(umin, uu);
-        umax = fmaxf(umax, uu);
-      }
-      const int ulo = (int)ceilf(fminf(fmaxf(umin - 0.05f, 0.0f), (float)a.n_u));
-      const int uhi = (int)floorf(fmaxf(fminf(umax + 0.05f, (float)(a.n_u - 1)), -1.0f));
-      // rows: extremes at the corners (the row through a point of a plane is
-      // linear in u, and monotone in the plane)
       const double* v = a.views + 12 * (size_t)c;
+      const TileWindow t = tile_window(v, a.proj + 12 * (size_t)c, cone, a.n_u, a.n_v, m, pm0, ra0,
+                                       z0, ZT);
       const bool flip = v[11] < 0.0;  // rows counted from the other end
-      double vmin = 1.0e300, vmax = -1.0e300, bmin = 1.0e300, bmax = 0.0;
-      bool any_m = false;
-#pragma unroll 1
-      for (int k = 0; k < 4; ++k) {
-        const double u = (double)((k & 1) ? uhi : ulo);
-        const Column col = column_line(v, cone, u);
-        any_m = any_m || col.m == m;
-        const double sm = m == 0 ? col.s0 : col.s1, rm = m == 0 ? col.r0 : col.r1;
-        const double t = ((double)((k & 2) ? pm0 + P - 1 : pm0) - sm) / rm;
-        const double d2 = v[5] + u * v[8] + (flip ? (double)(a.n_v - 1) * v[11] : 0.0);
-        const double A = cone ? v[2] + t * (d2 - v[2]) : d2 + t * v[2];
-        const double B = fabs(cone ? t * v[11] : v[11]);
-        vmin = fmin(vmin, ((double)z0 - 1.01 - A) / B);
-        vmax = fmax(vmax, ((double)(z0 + ZT) + 0.01 - A) / B);
-        bmin = fmin(bmin, B);
-        bmax = fmax(bmax, B);
-      }
+      const double bmin = t.bmin, bmax = t.bmax;
       Window w;
-      w.ulo = ulo;
-      w.uhi = uhi;
-      // (the host has bounded the window; the clamps only keep it in LDS)
-      w.v0 = (int)fmin(fmax(floor(vmin - 0.02), -1.0e9), 1.0e9);
-      w.nv = (int)fmin(fmax(ceil(vmax + 0.02) - (double)w.v0 + 1.0, 1.0), (double)(CAP - kRowPad));
+      w.ulo = t.ulo;
+      w.uhi = t.uhi;
+      // (the host has bounded the rows; the clamps only keep the window in LDS)
+      w.v0 = (int)fmin(fmax(t.v0, -1.0e9), 1.0e9);
+      w.nv = (int)fmin(fmax(t.v0 + t.rows - (double)w.v0, 1.0), (double)(CAP - kRowPad));
       w.n = (int)fmin(((double)ZL + 1.004) / bmin, 30000.0) + 1;
       w.kind = 0;
       auto offer = [&](auto n_) {
@@ -300,7 +242,7 @@ __global__ __launch_bounds__(P * 64) __attribute__((amdgpu_waves_per_eu(8))) voi
       if (flip) w.kind |= kFlip;
       s_win[lane] = w;
       const uint64_t some =
-          __ballot(gi < ngv && uhi >= ulo && any_m && w.v0 < a.n_v && w.v0 + w.nv > 0);
+          __ballot(gi < ngv && w.uhi >= w.ulo && t.any && w.v0 < a.n_v && w.v0 + w.nv > 0);
       if (lane == 0) s_mask = some;
     }
     __syncthreads();

@@ -30,7 +30,6 @@
 
 #include "gjp.h"
 #include "gjp_internal.h"
-#include "gjp_windows.h"
 
 using gjp::BatchInst;
 using gjp::FwdArgs;
@@ -306,7 +305,7 @@ static bool columns_share_inplane_setup(const gjp_geometry& g) {
 // Largest number of detector rows that any tile of the tile adjoint
 // (gjp_adjoint_tiles.hip) needs of a view, for 64 and 128 voxels along axis 2;
 // false if the geometry is not one it handles: column geometries in which every
-// source lies in front of all tiles (tiles reach up to 16 voxels past the
+// source lies in front of all tiles (tiles reach up to seven voxels past the
 // grid's upper ends), seen from every column.
 static bool tile_rows(const gjp_geometry& g, double rows[2]) {
   rows[0] = rows[1] = 0.0;
@@ -316,10 +315,13 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
     const double* o = g.views_grid.data() + 12 * (size_t)v;
     const double b1 = fabs(o[11]);
     if (!(b1 > 0.0)) return false;
-    double b_min = b1, near = 1.0e30, z_far = 1.0;
+    double b_min = b1, near = 1.0e30, z_far = 1.0, w_lo = 1.0;
+    const float* P = g.proj.data() + 12 * (size_t)v;
+    const double du = std::max(fabs(o[6]), fabs(o[7]));
+    double r_abs[2] = {0.0, 0.0}, d_m[2] = {1.0e30, 1.0e30};
     if (g.beam == GJP_CONE) {
-      const float* P = g.proj.data() + 12 * (size_t)v;
-      double w_lo = 1.0e300, w_hi = 0.0;
+      double w_hi = 0.0;
+      w_lo = 1.0e300;
       for (int k = 0; k < 4; ++k) {
         const double x = (k & 1) ? g.n[0] + kOver : -3.0, y = (k & 2) ? g.n[1] + kOver : -3.0;
         const double w = (double)P[8] * x + (double)P[9] * y + (double)P[11];
@@ -328,7 +330,7 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
       }
       if (!(w_lo > 1.0e-3 * w_hi)) return false;
       bool used[2] = {false, false};
-      double r_lo[2] = {1.0e300, 1.0e300}, r_hi[2] = {-1.0e300, -1.0e300}, r_abs[2] = {0.0, 0.0};
+      double r_lo[2] = {1.0e300, 1.0e300}, r_hi[2] = {-1.0e300, -1.0e300};
       for (int iu = 0; iu < g.n_u; ++iu) {
         const double r[2] = {o[3] + (double)iu * o[6] - o[0], o[4] + (double)iu * o[7] - o[1]};
         const int m = fabs(r[1]) > fabs(r[0]) ? 1 : 0;
@@ -346,6 +348,7 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
           d = o[m] - (g.n[m] + kOver - 3.0);
         else
           return false;
+        d_m[m] = d;
         near = std::min(near, d);
         z_far = std::max(fabs(o[2] + 2.0), fabs(g.n[2] + 130.0 - o[2]));
         b_min = std::min(b_min, b1 * d / r_abs[m]);
@@ -353,10 +356,24 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
     }
     // a tile's own extent, plus how far its rows shift over its planes and
     // columns (cone: the spread of the magnification at the far end of axis 2;
-    // parallel: rays climb less than one voxel per plane)
-    const double shift = g.beam == GJP_CONE ? 64.0 * z_far / near : 64.0;
+    // parallel: rays climb less than one voxel per plane): ordinarily far below these
+    double shift = g.beam == GJP_CONE ? 64.0 * z_far / near : 64.0;
+    // detectors nearly along their rays or climbing along axis 2: over the columns that a
+    // tile (up to 10.1 voxels wide) is seen by
+    double cols = 0.0;
+    for (int k = 0; k < 2; ++k) {
+      const double u = k * (g.n_u - 1.0);
+      cols = std::max(cols, 10.1 * (fabs(P[0] - u * P[8]) + fabs(P[1] - u * P[9])) / w_lo);
+    }
+    cols = std::min(cols + 1.2, g.n_u - 1.0);
+    if (g.beam == GJP_CONE) {
+      for (int m = 0; m < 2; ++m)
+        shift = std::max(shift, z_far * (7.0 * r_abs[m] / d_m[m] + du * cols) / d_m[m] / b1 * b_min);
+    } else {
+      shift = std::max(shift, fabs(o[2]) / std::max(fabs(o[0]), fabs(o[1])) * (7.0 + du * cols));
+    }
     for (int k = 0; k < 2; ++k)
-      rows[k] = std::max(rows[k], (64.0 * (k + 1) + 3.0 + shift) / b_min + 8.0);
+      rows[k] = std::max(rows[k], (64.0 * (k + 1) + 3.0 + shift) / b_min + fabs(o[8]) * cols / b1 + 8.0);
   }
   return true;
 }

@@ -32,7 +32,6 @@
 #include <type_traits>
 
 #include "gjp_internal.h"
-#include "gjp_windows.h"
 
 namespace gjp {
 

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "gjp_ray.h"
+#include "gjp_windows.h"
 
 struct gjp_geometry {
   uint64_t id;                     // unique per handle (never reused)
@@ -62,11 +63,6 @@ void timing_end(const char* name, TimedLaunch& t, hipStream_t s);
 // Empty entries after each detector column in the column-form ray table
 // (lets the adjoint read fixed-length candidate lists past a column's end).
 constexpr int kColumnPad = 8;
-
-// The tile adjoint (gjp_adjoint_tiles.hip): voxels of a tile along axes 0 and 1,
-// and the detector rows of one column that it can stage.
-constexpr int kTileEdge = 8;
-constexpr int kTileMaxRows = 7000;
 
 // View splits of the tile adjoint. Both axes in one launch, and the views split
 // so that it has about two rounds of workgroups (four per compute unit), with

@@ -176,9 +176,114 @@ static int rows_main() {
   return 0;
 }
 
+// Every window of the tile adjoint fits, and holds every ray that has weight in its tile.
+static void check_tile_windows(const gjp_geometry& g, long long* windows) {
+  const bool cone = g.beam == GJP_CONE;
+  const bool one = g.n[2] <= 64 || g.tile_rows[1] > gjp::kTileMaxRows;
+  const int zt = one ? 64 : 128, E = gjp::kTileEdge;
+  for (int view = 0; view < g.n_views; ++view) {
+    const double* v = g.views_grid.data() + 12 * (size_t)view;
+    const float* Q = g.proj.data() + 12 * (size_t)view;
+    const bool flip = v[11] < 0.0;
+    for (int m = 0; m < 2; ++m)
+      for (int p0 = 0; p0 < g.n[m]; p0 += E)
+        for (int ra0 = 0; ra0 < g.n[1 - m]; ra0 += E)
+          for (int z0 = 0; z0 < g.n[2]; z0 += zt) {
+            const gjp::TileWindow w =
+                gjp::tile_window(v, Q, cone, g.n_u, g.n_v, m, p0, ra0, z0, zt);
+            const bool used = w.uhi >= w.ulo && w.any && w.v0 < g.n_v && w.v0 + w.rows > 0;
+            if (used) {
+              ++*windows;
+              CHECK(w.rows <= gjp::kTileMaxRows);
+            }
+            for (int u = 0; u < g.n_u; u += 1 + g.n_u / 40) {
+              const gjp::Column c = gjp::column_line(v, cone, u);
+              if (c.m != m) continue;
+              const double sm = m == 0 ? c.s0 : c.s1, sa = m == 0 ? c.s1 : c.s0;
+              const double rm = m == 0 ? c.r0 : c.r1, ra = m == 0 ? c.r1 : c.r0;
+              for (int i = p0; i < std::min(p0 + E, g.n[m]); ++i) {
+                const double pa = sa + (i - sm) * (ra / rm), t = (i - sm) / rm;
+                if (!(pa > ra0 - 1.0 && pa < ra0 + E)) continue;
+                // rays of the column within a voxel of the tile along axis 2
+                const double d2 = v[5] + u * v[8];
+                const double A = cone ? v[2] + t * (d2 - v[2]) : d2 + t * v[2];
+                const double B = cone ? t * v[11] : v[11];
+                double k0 = (z0 - 1.0 - A) / B, k1 = (z0 + zt - A) / B;
+                if (k0 > k1) std::swap(k0, k1);
+                k0 = std::max(ceil(k0), 0.0);
+                k1 = std::min(floor(k1), g.n_v - 1.0);
+                if (k0 > k1) continue;
+                CHECK(used && u >= w.ulo && u <= w.uhi);
+                if (flip) {
+                  const double h = k0;
+                  k0 = g.n_v - 1 - k1;
+                  k1 = g.n_v - 1 - h;
+                }
+                CHECK(k0 >= w.v0 && k1 < w.v0 + w.rows);
+              }
+            }
+          }
+  }
+}
+
+static int tiles_main() {
+  int taken = 0, refused = 0;
+  long long windows = 0;
+  for (int trial = 0; trial < 3000; ++trial) {
+    const int n[3] = {integer(1, 40), integer(1, 40), integer(2, 300)};
+    const int beam = trial % 3 == 0 ? GJP_PARALLEL : GJP_CONE;
+    const int n_v = integer(2, 60), n_u = integer(1, 200);
+    const double reach = 0.5 * std::max(n[0], n[1]);
+    const double dist = reach + loguniform(4.0, 400.0), len = dist * uniform(1.05, 3.0);
+    const double pu = loguniform(0.05, 3.0), climb = uniform(-0.99, 0.99);
+    // columns that climb: along the detector, or more than it advances
+    const double su = trial % 4 == 0 ? pu * loguniform(0.1, 30.0) * (trial & 8 ? 1 : -1) : 0.0;
+    double views[24];
+    for (int k = 0; k < 2; ++k)
+      column_view(beam, uniform(0.0, 6.28), dist,
+                  beam == GJP_CONE ? climb * dist * uniform(0.0, 1.0) : climb * 0.7, len, pu,
+                  loguniform(0.01, 6.0) * (trial & 1 ? 1 : -1), su, n_u, n_v,
+                  uniform(-0.5, 0.5) * n_v, views + 12 * k);
+    if (trial % 5 == 0) {  // detectors nearly along the rays
+      const double a = uniform(1.4, 1.56);
+      for (int k = 0; k < 2; ++k) {
+        double* o = views + 12 * k;
+        const double x = cos(a) * o[6] - sin(a) * o[7], y = sin(a) * o[6] + cos(a) * o[7];
+        for (int j = 0; j < 2; ++j) o[3 + j] -= 0.5 * (n_u - 1) * ((j ? y : x) - o[6 + j]);
+        o[6] = x;
+        o[7] = y;
+      }
+    }
+    gjp_geometry* g = make(n, beam, 2, n_u, n_v, views);
+    CHECK(g != nullptr);
+    if (g->tiles) {
+      ++taken;
+      check_tile_windows(*g, &windows);
+    } else if (g->separable) {
+      ++refused;
+    }
+    gjp_destroy_geometry(g);
+  }
+  // columns ten voxels apart along axis 2, rays a fiftieth: more rows than fit
+  {
+    const int n[3] = {24, 24, 60};
+    double v[12];
+    for (double su = 0.0; su <= 12.0; su += 0.5) {
+      column_view(GJP_PARALLEL, 0.3, 0.0, 0.0, 0.0, 1.0, 0.02, su, 40, 3000, 0.0, v);
+      gjp_geometry* g = make(n, GJP_PARALLEL, 1, 40, 3000, v);
+      CHECK(su > 0.0 || g->tiles);
+      if (g->tiles) check_tile_windows(*g, &windows);
+      gjp_destroy_geometry(g);
+    }
+  }
+  CHECK(taken > 500 && windows > 4000 && refused > 20);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "rows")) rows_main();
+  else if (!strcmp(what, "tiles")) tiles_main();
   else {
     fprintf(stderr, "unknown part %s\n", what);
     return 2;

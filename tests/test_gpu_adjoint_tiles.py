@@ -86,3 +86,15 @@ def test_near_sources(gjp, oracle_mod, sod):
     sources lie inside the rule's margin and take the gather instead."""
     G = gjp.Geometry.circular_cone((30, 34, 40), 24, 90, 60, sod, sod + 40.0, 1.4, 1.4)
     _check(gjp, oracle_mod, G, 14, f"source at {sod}")
+
+
+@pytest.mark.parametrize("climb", [0.5, 6.0, 10.0, -10.0])
+def test_columns_that_climb(gjp, oracle_mod, climb):
+    """Neighbouring columns many rows apart along axis 2, rays a fiftieth of a voxel apart:
+    up to more detector rows per tile than its window holds (those take the gather)."""
+    shape, n_u, n_v = (24, 22, 60), 40, 3000
+    v = gjp.views_parallel(5, 1.0, 0.02, n_u, n_v)[1:3].copy()
+    v[:, 8] = climb
+    v[:, 5] -= climb * 0.5 * (n_u - 1)
+    G = gjp.Geometry(shape, v, n_u, n_v, beam="parallel")
+    _check(gjp, oracle_mod, G, 15, f"columns climbing {climb}")

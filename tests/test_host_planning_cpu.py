@@ -36,3 +36,7 @@ def driver(tmp_path_factory):
 
 def test_windows_of_the_row_forward_fit(driver):
     assert "rows: ok" in _run([driver, "rows"])
+
+
+def test_windows_of_the_tile_adjoint_fit_and_hold_their_rays(driver):
+    assert "tiles: ok" in _run([driver, "tiles"])
