@@ -93,6 +93,8 @@ __device__ __forceinline__ uint32_t lds_offset(const float* p) {
 // to LDS at dst + 4 lane, without a register. As assembly, because the compiler
 // would otherwise make every later LDS read wait for it; the caller waits
 // (vmcnt 0) before the barrier that publishes the data.
+// Writes m0, which the compiler reserves and takes no clobber of: between save_m0 and
+// restore_m0 only (around the loop and not in the block, which took 1% of the kernel).
 __device__ __forceinline__ void load_to_lds(u4rsrc rs, uint32_t off, uint32_t dst) {
   asm volatile(
       "s_mov_b32 m0, %2\n\t"
@@ -102,6 +104,12 @@ __device__ __forceinline__ void load_to_lds(u4rsrc rs, uint32_t off, uint32_t ds
       : "v"(off), "s"(rs), "s"(dst)
       : "memory");
 }
+__device__ __forceinline__ uint32_t save_m0() {
+  uint32_t x;
+  asm volatile("s_mov_b32 %0, m0" : "=s"(x));
+  return x;
+}
+__device__ __forceinline__ void restore_m0(uint32_t x) { asm volatile("s_mov_b32 m0, %0" : : "s"(x)); }
 
 __device__ __forceinline__ float clamp01(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
 
@@ -301,6 +309,7 @@ __global__ __launch_bounds__(P * 64) __attribute__((amdgpu_waves_per_eu(8))) voi
       const int vl = flip ? a.n_v - 1 - c.v0 - lane : c.v0 + lane;
       const int step = flip ? -64 : 64;
       const float* src = a.rays + ((size_t)c.view * a.n_u + c.u) * a.n_v;
+      const uint32_t m0 = save_m0();
       for (int k = pl; k < c.cols; k += P) {
         const uint64_t base = (uint64_t)(uintptr_t)(src + (size_t)k * a.n_v);
         const u4rsrc rs = {(uint32_t)base, (uint32_t)(base >> 32) & 0xffffu, (uint32_t)a.n_v * 4u,
@@ -310,6 +319,7 @@ __global__ __launch_bounds__(P * 64) __attribute__((amdgpu_waves_per_eu(8))) voi
         for (int e = 0; e < stride; e += 64, vi += step, dst += 256u)
           if (lane < stride - e) load_to_lds(rs, (uint32_t)vi * 4u, dst);
       }
+      restore_m0(m0);
     };
 
     auto compute = [&](const Chunk& c, const Lines& o) {
