@@ -1192,23 +1192,28 @@ static gjp_status back_project_tiles(const gjp_geometry* g, const double* d_view
       std::min<long long>(g->n_views, std::max<long long>(1, (long long)(kTileScratch / per_view)));
   const size_t vol = (size_t)g->n[0] * g->n[1] * g->n[2] * sizeof(float);
   void* rays = nullptr;
-  for (;;) {  // fewer views at a time where the device has no room for their rays
-    const int splits = gjp::adjoint_tile_splits(g->n, (int)chunk);
-    const size_t bytes = (((size_t)chunk * per_view + 255) & ~(size_t)255) + 2 * splits * vol;
-    const hipError_t e = scratch_alloc(&rays, bytes, s);
+  size_t ray_bytes = 0, part = 0;
+  for (bool parts = true;;) {  // fewer views at a time where the device has no room for their rays
+    part = parts ? 2 * (size_t)gjp::adjoint_tile_splits(g->n, (int)chunk) * vol : 0;
+    ray_bytes = ((size_t)chunk * per_view + 255) & ~(size_t)255;
+    const hipError_t e = scratch_alloc(&rays, ray_bytes + part, s);
     if (e == hipSuccess) break;
-    if (e != hipErrorOutOfMemory || chunk == 1) return hip_fail(e, "back_project: scaled rays");
+    if (e != hipErrorOutOfMemory || (chunk == 1 && part == 0))
+      return hip_fail(e, "back_project: scaled rays");
     (void)hipGetLastError();
+    if (chunk == 1) parts = false;  // then without partial volumes
     chunk = (chunk + 3) / 4;
   }
+  const float4* parts = part ? reinterpret_cast<const float4*>(static_cast<char*>(rays) + ray_bytes)
+                             : nullptr;
   int st = GJP_OK;
   for (int v0 = 0; v0 < g->n_views && st == GJP_OK; v0 += (int)chunk) {
     const int nc = (int)std::min<long long>(chunk, g->n_views - v0);
     st = gjp::launch_adjoint_value_table(g, d_views, d_sino, v0, nc, static_cast<float*>(rays),
                                          nullptr, nullptr, s);
     if (st == GJP_OK)
-      st = gjp::launch_adjoint_gather(g, d_proj, nullptr, nullptr, static_cast<float*>(rays),
-                                      nullptr, nullptr, v0, 0, nc, v0 > 0, d_vol, s);
+      st = gjp::launch_adjoint_gather(g, d_proj, nullptr, parts, static_cast<float*>(rays), nullptr,
+                                      nullptr, v0, 0, nc, v0 > 0, d_vol, s);
   }
   const hipError_t e = scratch_free(rays, s);
   if (st != GJP_OK) return (gjp_status)st;
@@ -1244,13 +1249,18 @@ extern "C" gjp_status gjp_back_project(const gjp_geometry* g, const float* d_sin
   void* table = nullptr;
   void* mask = nullptr;
   void* cols = nullptr;
-  // (the general gather's partial volumes follow the table)
-  const size_t part =
-      g->free_gather ? (size_t)gjp::adjoint_free_splits(g->n, (int)chunk) * g->n[0] * g->n[1] *
-                           g->n[2] * sizeof(float)
-                     : 0;
-  GJP_HIP(scratch_alloc(&table, (size_t)chunk * per_view * entry + part, s), "back_project: table");
-  hipError_t e = scratch_alloc(&mask, (size_t)chunk * sizeof(int), s);
+  // (the general gather's partial volumes follow the table, where there is room for them)
+  const size_t splits = g->free_gather ? (size_t)gjp::adjoint_free_splits(g->n, (int)chunk) : 1;
+  const size_t table_bytes = (size_t)chunk * per_view * entry;
+  size_t part = splits > 1 ? splits * g->n[0] * g->n[1] * g->n[2] * sizeof(float) : 0;
+  hipError_t e = scratch_alloc(&table, table_bytes + part, s);
+  if (e == hipErrorOutOfMemory && part) {
+    (void)hipGetLastError();
+    part = 0;
+    e = scratch_alloc(&table, table_bytes, s);
+  }
+  GJP_HIP(e, "back_project: table");
+  e = scratch_alloc(&mask, (size_t)chunk * sizeof(int), s);
   if (e == hipSuccess && col_entry > 0)
     e = scratch_alloc(&cols, (size_t)chunk * g->n_u * col_entry, s);
   if (e != hipSuccess) {
@@ -1260,6 +1270,7 @@ extern "C" gjp_status gjp_back_project(const gjp_geometry* g, const float* d_sin
   }
   float4* t4 = value ? nullptr : static_cast<float4*>(table);
   float4* c4 = value ? nullptr : static_cast<float4*>(cols);
+  if (part) c4 = reinterpret_cast<float4*>(static_cast<char*>(table) + table_bytes);
   float* tv = value ? static_cast<float*>(table) : nullptr;
   gjp::ResCol* cv = value ? static_cast<gjp::ResCol*>(cols) : nullptr;
   for (int v0 = 0; v0 < g->n_views && st == GJP_OK; v0 += (int)chunk) {

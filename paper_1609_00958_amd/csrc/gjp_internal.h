@@ -188,11 +188,13 @@ int launch_adjoint_free(const gjp_geometry* g, const float* proj, const float4* 
                         const int* mask, int n_views, bool accumulate, float* vol, float* part,
                         int splits, hipStream_t s);
 // launch_adjoint_value_table without cols writes launch_adjoint_scale's rays.
-// Column gather from the ray table (table, cols) or, if vals and rcols are not
-// null, from the value table (vals, rcols); vals without rcols: the scaled rays
-// of launch_adjoint_tiles, followed (from the next multiple of 64 values) by
-// its partial volumes; other geometries: free gather (table, followed by its
-// partial volumes) or tile splat (table).
+// launch_adjoint_gather, by the pointers that are not null:
+//   vals, rcols     column gather from the value table
+//   vals            tile adjoint; vals: the scaled rays, cols: scratch for the partial
+//                   volumes of adjoint_tile_splits, or null (none, also if those are 0)
+//   table           column geometries: column gather from the ray table (and cols);
+//                   general ones: cube gather (cols: scratch for the partial volumes of
+//                   adjoint_free_splits, or null: none) or tile splat
 int launch_adjoint_gather(const gjp_geometry* g, const float* proj, const float4* table,
                           const float4* cols, const float* vals, const ResCol* rcols,
                           const int* mask, int view0, int c0, int n_chunk, bool accumulate,

@@ -2199,9 +2199,8 @@ int launch_adjoint_gather(const gjp_geometry* g, const float* proj, const float4
   if (vals && !rcols) {
     const double* views = nullptr;
     int st = geometry_device(g, &views, &proj);
-    const int splits = adjoint_tile_splits(g->n, n_chunk);
-    const size_t n_rays = (size_t)n_chunk * g->n_u * g->n_v;
-    float* part = splits ? const_cast<float*>(vals) + ((n_rays + 63) & ~(size_t)63) : nullptr;
+    const int splits = cols ? adjoint_tile_splits(g->n, n_chunk) : 0;
+    float* part = splits ? reinterpret_cast<float*>(const_cast<float4*>(cols)) : nullptr;
     if (st == 0)
       st = launch_adjoint_tiles(g, views + 12 * (size_t)view0, proj + 12 * (size_t)view0, vals,
                                 n_chunk, accumulate, vol, part, splits, s);
@@ -2234,11 +2233,10 @@ int launch_adjoint_gather(const gjp_geometry* g, const float* proj, const float4
   } else {
     if (c0 != 0) return set_error(-4, "adjoint: the tile splat takes whole chunks");
     if (g->free_gather) {
-      const size_t n_rays = (size_t)n_chunk * g->n_u * g->n_v;
-      const int st = launch_adjoint_free(
-          g, proj + 12 * (size_t)view0, table, mask, n_chunk, accumulate, vol,
-          reinterpret_cast<float*>(const_cast<float4*>(table) + 2 * n_rays),
-          adjoint_free_splits(g->n, n_chunk), s);
+      const int st = launch_adjoint_free(g, proj + 12 * (size_t)view0, table, mask, n_chunk,
+                                         accumulate, vol,
+                                         reinterpret_cast<float*>(const_cast<float4*>(cols)),
+                                         cols ? adjoint_free_splits(g->n, n_chunk) : 1, s);
       timing_end("adjoint_gather", t, s);
       return st;
     }

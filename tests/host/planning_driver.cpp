@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <map>
 #include <vector>
 
 #include "gjp.h"
@@ -27,9 +28,18 @@ int launch_forward_naive(const GridGeom&, const double*, const void*, int, int, 
                          float*, hipStream_t) { return 0; }
 int launch_adjoint_table(const gjp_geometry*, const double*, const float*, int, int, float4*,
                          float4*, int*, hipStream_t) { return 0; }
-int launch_adjoint_gather(const gjp_geometry*, const float*, const float4*, const float4*,
-                          const float*, const ResCol*, const int*, int, int, int, bool, float*,
-                          hipStream_t) { return 0; }
+struct Gather {
+  const void *table, *cols, *vals, *rcols;
+  int view0, c0, n;
+  bool accumulate;
+};
+static std::vector<Gather> g_gathers;
+int launch_adjoint_gather(const gjp_geometry*, const float*, const float4* table,
+                          const float4* cols, const float* vals, const ResCol* rcols, const int*,
+                          int view0, int c0, int n, bool accumulate, float*, hipStream_t) {
+  g_gathers.push_back({table, cols, vals, rcols, view0, c0, n, accumulate});
+  return 0;
+}
 int launch_adjoint_value_table(const gjp_geometry*, const double*, const float*, int, int, float*,
                                ResCol*, int*, hipStream_t) { return 0; }
 int launch_batched_pad(const BatchInst*, int, hipStream_t) { return 0; }
@@ -39,6 +49,41 @@ int batched_grid_size(int) { return 1; }
 size_t dtype_size(int dtype) { return dtype == 0 ? 4 : 2; }
 int noalloc_scratch(void**) { return -1; }
 }  // namespace gjp
+
+// Device memory, as far as the host path takes it: blocks of a given total at most, not
+// backed by memory of their size (the stand-ins read none).
+static size_t g_free_bytes = (size_t)1 << 60, g_largest = 0;
+static std::map<void*, size_t> g_blocks;
+static hipError_t take(void** p, size_t n) {
+  if (n > g_free_bytes) return hipErrorOutOfMemory;
+  g_free_bytes -= n;
+  g_largest = std::max(g_largest, n);
+  *p = aligned_alloc(256, 256);
+  g_blocks[*p] = n;
+  return hipSuccess;
+}
+static hipError_t give(void* p) {
+  if (!p) return hipSuccess;
+  g_free_bytes += g_blocks.at(p);
+  g_blocks.erase(p);
+  free(p);
+  return hipSuccess;
+}
+extern "C" {
+hipError_t hipGetDevice(int* d) {
+  *d = 0;
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) { return take(p, n); }
+hipError_t hipFree(void* p) { return give(p); }
+hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) { return take(p, n); }
+hipError_t hipFreeAsync(void* p, hipStream_t) { return give(p); }
+hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t*, int) { return hipErrorNotSupported; }
+}
 
 static int bad = 0;
 #define CHECK(c)                                                   \
@@ -280,10 +325,105 @@ static int tiles_main() {
   return 0;
 }
 
+// One call of the adjoint with `room` bytes free: its status, the launches it made, and
+// that it gave back what it took.
+static gjp_status back(const gjp_geometry* g, size_t room) {
+  gjp::g_gathers.clear();
+  g_largest = 0;
+  const double* views;
+  const float* proj;
+  g_free_bytes = (size_t)1 << 60;
+  CHECK(gjp::geometry_device(g, &views, &proj) == GJP_OK);
+  g_free_bytes = room;
+  const gjp_status st = gjp_back_project(g, (const float*)16, (float*)16, nullptr);
+  CHECK(g_free_bytes == room);
+  g_free_bytes = (size_t)1 << 60;
+  if (st != GJP_OK) return st;
+  // every view once, in order; all but the first launch add
+  int next = 0;
+  for (const auto& q : gjp::g_gathers) {
+    CHECK(q.view0 + q.c0 == next && q.accumulate == (next > 0));
+    next += q.n;
+  }
+  CHECK(next == g->n_views);
+  return st;
+}
+
+static int scratch_main() {
+  const int n[3] = {64, 64, 64};
+  std::vector<double> v(12 * 40);
+  {  // scaled rays of a view 64 MiB: 32 views in 2 GiB, then 8; two partial volumes per split
+    CHECK(gjp_views_circular_cone(40, 256, 512, 0.05, 0.15, 4096, 4096, v.data()) == GJP_OK);
+    gjp_geometry* g = make(n, GJP_CONE, 40, 4096, 4096, v.data());
+    CHECK(g && g->tiles);
+    const size_t view = (size_t)4096 * 4096 * 4, vol = (size_t)64 * 64 * 64 * 4;
+    CHECK(back(g, (size_t)1 << 40) == GJP_OK && gjp::g_gathers.size() == 2);
+    CHECK(gjp::g_gathers[0].n == 32 && gjp::g_gathers[0].cols && !gjp::g_gathers[0].rcols);
+    CHECK(g_largest >= 32 * view + 2 * gjp::adjoint_tile_splits(n, 32) * vol);
+    // less room: quarters of the views, and at last one view without partial volumes
+    CHECK(back(g, 20 * view) == GJP_OK && gjp::g_gathers[0].n == 8 && gjp::g_gathers[0].cols);
+    CHECK(back(g, 3 * view) == GJP_OK && gjp::g_gathers[0].n == 2 && gjp::g_gathers[0].cols);
+    CHECK(back(g, view + 2 * vol) == GJP_OK && gjp::g_gathers[0].n == 1 && gjp::g_gathers[0].cols);
+    CHECK(back(g, view) == GJP_OK && gjp::g_gathers.size() == 40 && !gjp::g_gathers[0].cols);
+    CHECK(back(g, view - 1) == GJP_ENOMEM);
+    gjp_destroy_geometry(g);
+  }
+  {  // general geometries: what sufficed for the ray table suffices
+    const int big[3] = {128, 128, 128};
+    CHECK(gjp_views_circular_cone(40, 512, 1024, 2, 2, 200, 200, v.data()) == GJP_OK);
+    for (int k = 0; k < 40; ++k) v[12 * k + 9] = 0.3;
+    gjp_geometry* g = make(big, GJP_CONE, 40, 200, 200, v.data());
+    CHECK(g && g->free_gather);
+    const size_t table = (size_t)40 * 200 * 200 * 32, vol = (size_t)128 * 128 * 128 * 4;
+    const size_t splits = gjp::adjoint_free_splits(big, 40);
+    CHECK(splits > 1);
+    CHECK(back(g, (size_t)1 << 40) == GJP_OK && gjp::g_gathers[0].cols);
+    CHECK(g_largest == table + splits * vol);
+    CHECK(back(g, table + splits * vol + 4096) == GJP_OK && gjp::g_gathers[0].cols);
+    CHECK(back(g, table + splits * vol - 1) == GJP_OK && !gjp::g_gathers[0].cols);
+    CHECK(back(g, table + 4096) == GJP_OK && !gjp::g_gathers[0].cols);
+    CHECK(back(g, table - 1) == GJP_ENOMEM);
+    gjp_destroy_geometry(g);
+  }
+  return 0;
+}
+
+// The kernels that geometries of each kind are sent to.
+static int dispatch_main() {
+  const int n[3] = {64, 60, 70};
+  std::vector<double> v(12 * 30);
+  gjp_geometry* g;
+  CHECK(gjp_views_circular_cone(30, 256, 512, 2, 2, 64, 64, v.data()) == GJP_OK);
+  g = make(n, GJP_CONE, 30, 64, 64, v.data());  // ordinary circular scan
+  CHECK(g && g->separable && g->rows > 0 && g->tiles && !g->free_gather);
+  gjp_destroy_geometry(g);
+  CHECK(gjp_views_parallel(30, 1, 1, 90, 80, v.data()) == GJP_OK);
+  g = make(n, GJP_PARALLEL, 30, 90, 80, v.data());
+  CHECK(g && g->separable && g->rows > 0 && g->tiles && !g->free_gather);
+  gjp_destroy_geometry(g);
+  CHECK(gjp_views_circular_cone(30, 48, 512, 2, 0.1, 64, 64, v.data()) == GJP_OK);
+  g = make(n, GJP_CONE, 30, 64, 64, v.data());  // sources too near for the tiles
+  CHECK(g && g->separable && !g->tiles && !g->free_gather);
+  gjp_destroy_geometry(g);
+  CHECK(gjp_views_circular_cone(30, 256, 512, 2, 2, 64, 64, v.data()) == GJP_OK);
+  for (int k = 0; k < 30; ++k) v[12 * k + 9] = 0.3;  // tilted detectors
+  g = make(n, GJP_CONE, 30, 64, 64, v.data());
+  CHECK(g && !g->separable && !g->rows && !g->tiles && g->free_gather);
+  gjp_destroy_geometry(g);
+  for (int k = 0; k < 30; ++k)  // and sources inside the grid
+    for (int j = 0; j < 3; ++j) v[12 * k + j] *= 0.05;
+  g = make(n, GJP_CONE, 30, 64, 64, v.data());
+  CHECK(g && !g->separable && !g->rows && !g->tiles && !g->free_gather);
+  gjp_destroy_geometry(g);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "rows")) rows_main();
   else if (!strcmp(what, "tiles")) tiles_main();
+  else if (!strcmp(what, "scratch")) scratch_main();
+  else if (!strcmp(what, "dispatch")) dispatch_main();
   else {
     fprintf(stderr, "unknown part %s\n", what);
     return 2;

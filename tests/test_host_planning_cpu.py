@@ -1,7 +1,8 @@
-"""The library's host rules on the CPU: every geometry that a rule sends to a kernel has
-windows that fit that kernel's LDS arrays. csrc/gjp_api.cpp is compiled for the host and
-driven by tests/host/planning_driver.cpp, over random geometries and the ones at a rule's
-edge."""
+"""The library's host rules on the CPU: which kernels a geometry is sent to, that every
+geometry that a rule sends to a kernel has windows that fit that kernel's LDS arrays, and
+what the adjoint does where the device has little room. csrc/gjp_api.cpp is compiled for
+the host and driven by tests/host/planning_driver.cpp, over random geometries and the
+ones at a rule's edge, with stand-ins for the launchers and the allocator."""
 import os
 import subprocess
 
@@ -40,3 +41,11 @@ def test_windows_of_the_row_forward_fit(driver):
 
 def test_windows_of_the_tile_adjoint_fit_and_hold_their_rays(driver):
     assert "tiles: ok" in _run([driver, "tiles"])
+
+
+def test_adjoint_scratch_at_its_limits(driver):
+    assert "scratch: ok" in _run([driver, "scratch"])
+
+
+def test_dispatch(driver):
+    assert "dispatch: ok" in _run([driver, "dispatch"])
