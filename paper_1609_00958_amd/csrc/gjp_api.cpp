@@ -550,7 +550,7 @@ extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geomet
   double rows[2];
   g->rows = rows_per_lane(*g);
   g->free_gather = gathers_freely(*g);
-  g->tiles = tile_rows(*g, rows) && rows[0] <= gjp::kTileMaxRows;
+  g->tiles = tile_rows(*g, rows) && rows[0] <= gjp::kTileMaxRows && g->n_u <= gjp::kTileMaxColumns;
   for (int k = 0; k < 2; ++k) g->tile_rows[k] = g->tiles ? (int)std::min(rows[k], 1.0e9) : 0;
   *out = g.release();
   return GJP_OK;
@@ -1181,7 +1181,8 @@ extern "C" gjp_status gjp_get_forward_tile(const gjp_geometry* g, int32_t vol_dt
 static const int kGatherViews = 32;
 
 // The tile adjoint over chunks of views (scaled rays: one sinogram's bytes per
-// chunk, at most kTileScratch or one view).
+// chunk, at most kTileScratch or one view; a wavefront each of at most 2^32 threads'
+// for its columns).
 static const size_t kTileScratch = (size_t)2 << 30;
 
 static gjp_status back_project_tiles(const gjp_geometry* g, const double* d_views,
@@ -1190,6 +1191,7 @@ static gjp_status back_project_tiles(const gjp_geometry* g, const double* d_view
   const size_t per_view = (size_t)g->n_u * (size_t)g->n_v * sizeof(float);
   long long chunk =
       std::min<long long>(g->n_views, std::max<long long>(1, (long long)(kTileScratch / per_view)));
+  chunk = std::min<long long>(chunk, std::max(1, gjp::kTileMaxColumns / g->n_u));
   const size_t vol = (size_t)g->n[0] * g->n[1] * g->n[2] * sizeof(float);
   void* rays = nullptr;
   size_t ray_bytes = 0, part = 0;

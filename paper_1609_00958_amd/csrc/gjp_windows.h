@@ -48,10 +48,12 @@ GJP_HD bool row_window(double A, double B, double C, double D, double t0, int pl
 // Planes whose windows a block of np planes needs: the loop's, in whole steps.
 GJP_HD int row_planes(int np) { return (np + kRowStep - 1) & ~(kRowStep - 1); }
 
-// Tile adjoint (gjp_adjoint_tiles.hip): voxels of a tile along axes 0 and 1, and the
-// detector rows of one column that it can stage.
+// Tile adjoint (gjp_adjoint_tiles.hip): voxels of a tile along axes 0 and 1, the
+// detector rows of one column that it can stage, and the detector columns that one
+// launch scales (a wavefront each, below 2^32 threads).
 constexpr int kTileEdge = 8;
 constexpr int kTileMaxRows = 7000;
+constexpr int kTileMaxColumns = (1 << 26) - 4;
 
 // In-plane part of a column's rays: origin s, direction r on axes 0 and 1 (the
 // arithmetic of ray_line, in which dv_0 = dv_1 = 0 adds nothing) and the

@@ -368,6 +368,16 @@ static int scratch_main() {
     CHECK(back(g, view - 1) == GJP_ENOMEM);
     gjp_destroy_geometry(g);
   }
+  {  // fan beams, one row: no more columns per launch than 2^32 threads scale
+    const int flat[3] = {64, 64, 1};
+    std::vector<double> w(12 * 20000);
+    CHECK(gjp_views_circular_cone(20000, 256, 512, 0.03, 1.0, 4096, 1, w.data()) == GJP_OK);
+    gjp_geometry* g = make(flat, GJP_CONE, 20000, 4096, 1, w.data());
+    CHECK(g && g->tiles);
+    CHECK(back(g, (size_t)1 << 40) == GJP_OK && gjp::g_gathers.size() > 1);
+    for (const auto& q : gjp::g_gathers) CHECK(((long long)q.n * 4096 + 3) / 4 * 256 < (1ll << 32));
+    gjp_destroy_geometry(g);
+  }
   {  // general geometries: what sufficed for the ray table suffices
     const int big[3] = {128, 128, 128};
     CHECK(gjp_views_circular_cone(40, 512, 1024, 2, 2, 200, 200, v.data()) == GJP_OK);
