@@ -433,6 +433,50 @@ static bool gathers_freely(const gjp_geometry& g) {
   return true;
 }
 
+// Launch of a general geometry's forward (FwdArgs::spread): tile shape and whether its
+// tiles are dealt to the XCDs. Dealt tiles end evenly and take four planes' loads
+// together, but neighbouring tiles read the volume through different L2s. That costs
+// where rays lie more than a voxel or two apart and there are tiles enough to fill the
+// chip without it (120 x 130 x 110, 48 views of 60^2 152 us dealt, 89 in groups of views;
+// 140^2 254 and 297, 400^2 421 and 926; 30^2, fewer tiles than compute units, 53 and
+// 84; 240^3, 200^2 1.38 and 1.80 ms), and in views whose columns lie along axis 2, where
+// groups take the row-uniform loop (128^3, wide cone, 324 and 242 us). Few columns:
+// wavefronts along v (60^3, 400 views of 1 x 400 82 us with 16 x 16 tiles, 36 with 4 x 64;
+// in groups 42). Few rows: groups' tiles are 64 rows long (48 views of 400 x 4 73 and
+// 125 us; fewer tiles than half the compute units, one row 46 and 34).
+static bool deals_tiles_by_rule(const gjp_geometry& g, int& tile) {
+  tile = 4;
+  if (g.separable) return false;
+  // pixels per voxel along u and v at the grid's centre, and views with columns along axis 2
+  double pu = 0.0, pv = 0.0;
+  int columns = 0;
+  for (int v = 0; v < g.n_views; ++v) {
+    const float* P = g.proj.data() + 12 * (size_t)v;
+    double n[3] = {P[3], P[7], P[11]}, gu = 0.0, gv = 0.0;
+    for (int k = 0; k < 3; ++k)
+      for (int r = 0; r < 3; ++r) n[r] += 0.5 * (g.n[k] - 1) * P[4 * r + k];
+    for (int k = 0; k < 3; ++k) {
+      const double u = P[k] - n[0] / n[2] * P[8 + k], w = P[4 + k] - n[1] / n[2] * P[8 + k];
+      gu += u * u;
+      gv += w * w;
+    }
+    pu += sqrt(gu) / fabs(n[2]);
+    pv += sqrt(gv) / fabs(n[2]);
+    const double* o = g.views_grid.data() + 12 * (size_t)v;
+    columns += o[9] == 0.0 && o[10] == 0.0;
+  }
+  pu /= g.n_views;
+  pv /= g.n_views;
+  // lanes along v where there are few columns
+  tile = g.n_u <= 4 || (g.n_u <= 12 && pv >= 8.0 * pu) ? 6 : g.n_u <= 8 ? 5 : 4;
+  const double tiles = (double)g.n_views * ceil((double)g.n_u / gjp::tile_u_columns(tile)) *
+                       ceil((double)g.n_v / gjp::tile_v_pixels(tile));
+  if (2 * columns > g.n_views || tiles > 1.0e6) return false;
+  if (g.n_v < 16) return g.n_v > 2 || tiles > 128.0;
+  if (g.n_u <= 4) return g.n_u == 1 || tiles <= 1024.0;
+  return tiles <= (g.n_u < 16 ? 256.0 : 512.0) || tiles * std::max(pu, pv) >= 950.0;
+}
+
 // Rays per lane of the row forward (gjp_forward_rows.hip), or 0 where the padded
 // copies are sampled instead: not a column geometry, rays so far apart that 128
 // of them span more than the window, or too few rays in a column to share its
@@ -442,7 +486,8 @@ static bool gathers_freely(const gjp_geometry& g) {
 // wavefront of the copies' kernel 0.92 per 64 rays; their two copies take 14 us
 // and 6.5 ps per voxel. 64^3, 64 x 64 rays: 22 against 31 us for 64 views, 93
 // against 64 us for 360.
-static int rows_per_lane(const gjp_geometry& g) {
+static int rows_per_lane(const gjp_geometry& g, bool& pay) {
+  pay = false;
   if (!g.separable) return 0;
   const double s0 = (double)g.n[1] * g.n[2] * 4.0, s1 = (double)g.n[2] * 4.0;
   if (66.0 * (s0 + s1) >= 2147483648.0) return 0;  // 31-bit offsets within 64 planes
@@ -463,8 +508,8 @@ static int rows_per_lane(const gjp_geometry& g) {
   }
   const double planes = (double)std::max(g.n[0], g.n[1]) * g.n_u * g.n_views;
   const double voxels = (double)g.n[0] * g.n[1] * g.n[2];
-  if (28.0e-12 * planes * (best_cost - 0.92 * ceil(g.n_v / 64.0)) > 14.0e-6 + 6.5e-12 * voxels)
-    return 0;
+  pay = best > 0 &&
+        28.0e-12 * planes * (best_cost - 0.92 * ceil(g.n_v / 64.0)) <= 14.0e-6 + 6.5e-12 * voxels;
   return best;
 }
 
@@ -548,7 +593,8 @@ extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geomet
   }
   g->separable = columns_share_inplane_setup(*g);
   double rows[2];
-  g->rows = rows_per_lane(*g);
+  g->rows = rows_per_lane(*g, g->rows_pay);
+  g->deal = deals_tiles_by_rule(*g, g->deal_tile);
   g->free_gather = gathers_freely(*g);
   g->tiles = tile_rows(*g, rows) && rows[0] <= gjp::kTileMaxRows && g->n_u <= gjp::kTileMaxColumns;
   for (int k = 0; k < 2; ++k) g->tile_rows[k] = g->tiles ? (int)std::min(rows[k], 1.0e9) : 0;
@@ -800,13 +846,16 @@ std::string device_tag() {
 }
 
 // Cache file: one entry per line, "<device> <key> <tile_v_log2> <view_group>
-// <load_group>"; lines that do not parse are ignored.
+// <load_group>", and FwdTile::path where it is not the geometry's default; lines that do
+// not parse are ignored.
 bool parse_entry(const std::string& line, std::string& dev, std::string& key, FwdTile& t) {
   std::istringstream in(line);
   int k = 0, vg = 0, rg = 0;
   if (!(in >> dev >> key >> k >> vg >> rg)) return false;
   if (k < 4 || k > 8 || vg < 1 || vg > 64 || (rg != 2 && rg != 4)) return false;
   t = FwdTile();
+  int path = FwdTile::BY_RULE;
+  if (in >> path && (path == FwdTile::OWN || path == FwdTile::TILES)) t.path = path;
   t.tile_v_log2 = k;
   t.view_group = vg;
   t.ru_group = rg;
@@ -843,8 +892,8 @@ void disk_store(const std::string& dev, const std::string& key, const FwdTile& t
     }
   }
   char buf[512];
-  snprintf(buf, sizeof(buf), "%s %s %d %d %d", dev.c_str(), key.c_str(), t.tile_v_log2,
-           t.view_group, t.ru_group);
+  snprintf(buf, sizeof(buf), t.path == FwdTile::BY_RULE ? "%s %s %d %d %d" : "%s %s %d %d %d %d",
+           dev.c_str(), key.c_str(), t.tile_v_log2, t.view_group, t.ru_group, t.path);
   lines.push_back(buf);
   const std::string tmp = std::string(path) + ".tmp" + std::to_string((long)getpid());
   {
@@ -882,7 +931,8 @@ long long padded_elems(const int* n) {
 // Rays per lane of the row forward, or 0 where the padded copies are sampled.
 // 16-bit rows that do not all start on 4 bytes would have to be read element by
 // element: 81 us instead of 42 for FP16 97 x 83 x 121 and 45 views of 129 x 101.
-int rows_of(const gjp_geometry* g, const void* d_vol, int dtype) {
+int rows_of(const gjp_geometry* g, const void* d_vol, int dtype, const FwdTile& tile) {
+  if (tile.path == FwdTile::BY_RULE ? !g->rows_pay : tile.path == FwdTile::TILES) return 0;
   return dtype == GJP_F32 || (g->n[2] % 2 == 0 && (uintptr_t)d_vol % 4 == 0) ? g->rows : 0;
 }
 
@@ -918,14 +968,17 @@ void fill_fwd_args(const gjp_geometry* g, const double* d_views, int rows, float
   a.spread = 0;
 }
 
-// General geometries: 16 x 16 pixels per workgroup and tiles dealt to the XCDs, the
-// whole columns if there are eight. Their views are unlike, and tiles at the
-// detector's ends miss the volume, so XCDs with whole views each ended far apart, and
-// every view read the whole copies through one L2: 120 x 136 x 112, 48 views of
-// 180 x 200 530 us with groups of eight views of 64 x 4 tiles, 397 view by view, 350
-// dealt (16 x 16 and 32 x 8 alike); 128^3, 12 views of 700^2 588 -> 181 us.
+// General geometries' own launch: tiles dealt to the XCDs, whole columns of tiles if there
+// are eight. Their views are unlike, and tiles at the detector's ends miss the volume, so
+// XCDs with whole views each ended far apart, and every view read the whole copies through
+// one L2: 120 x 136 x 112, 48 views of 180 x 200 530 us with groups of eight views of 64 x
+// 4 tiles, 397 view by view, 350 dealt (16 x 16 and 32 x 8 alike); 128^3, 12 views of 700^2
+// 588 -> 181 us.
+bool deals_tiles(const gjp_geometry* g, const FwdTile& tile) {
+  return !g->separable && (tile.path == FwdTile::OWN || (tile.path == FwdTile::BY_RULE && g->deal));
+}
 void spread_tiles(const gjp_geometry* g, FwdArgs& a) {
-  const int k = 4;
+  const int k = g->deal_tile;
   a.tile_v_log2 = k;
   a.tiles_v = (g->n_v + gjp::tile_v_pixels(k) - 1) / gjp::tile_v_pixels(k);
   a.tiles_u = (g->n_u + gjp::tile_u_columns(k) - 1) / gjp::tile_u_columns(k);
@@ -980,9 +1033,9 @@ gjp_status validate_fwd(const gjp_geometry* g, const void* d_vol, int32_t dtype,
 int forward_into(const gjp_geometry* g, const double* d_views, const void* d_vol, int dtype,
                  float* d_sino, void* padded, hipStream_t s, const FwdTile& tile) {
   FwdArgs a;
-  const int rows = rows_of(g, d_vol, dtype);
+  const int rows = rows_of(g, d_vol, dtype, tile);
   fill_fwd_args(g, d_views, rows, d_sino, tile, a);
-  if (!g->separable) spread_tiles(g, a);
+  if (deals_tiles(g, tile)) spread_tiles(g, a);
   if (rows) {
     a.vol = d_vol;
     return gjp::launch_forward(a, dtype, g->weight, false, g->n_views, s);
@@ -1003,7 +1056,7 @@ gjp_status forward_with_tile(const gjp_geometry* g, const void* d_vol, int32_t d
   if (st != GJP_OK) return (gjp_status)st;
   if (!block_fits_32bit(g->n, dtype))
     return fail(GJP_EUNSUPPORTED, "forward: volume planes too large for 32-bit block offsets");
-  if (rows_of(g, d_vol, dtype))
+  if (rows_of(g, d_vol, dtype, tile))
     return (gjp_status)forward_into(g, d_views, d_vol, dtype, d_sino, nullptr, s, tile);
   void* padded = nullptr;
   GJP_HIP(scratch_alloc(&padded, (size_t)(2 * copy_bytes(g->n, dtype)), s),
@@ -1089,27 +1142,34 @@ extern "C" gjp_status gjp_autotune_forward(const gjp_geometry* g, const void* d_
     }
     return GJP_OK;
   };
-  // tile shape and view group with four-plane load groups, then two-plane
-  // groups for the best of them
-  // two rays per lane (k = 7) only for 16-bit storage; three (k = 8) for all
-  // (the row forward has no tile shapes: view groups only; general geometries have
-  // one configuration)
-  const bool pairs = vol_dtype != GJP_F32, rows = rows_of(g, d_vol, vol_dtype) != 0;
-  for (int k : {8, 7, 6, 5, 4}) {
-    if ((k == 7 && !pairs) || (k != 6 && rows)) continue;
+  // The geometry's own kernel first (the row forward, which has no tile shapes: view
+  // groups only; the dealt tiles of general geometries, one configuration), then the
+  // padded copies: tile shape and view group with four-plane load groups, then two-plane
+  // groups for the best of them. Two rays per lane (k = 7) only for 16-bit storage;
+  // three (k = 8) for all.
+  const bool pairs = vol_dtype != GJP_F32;
+  FwdTile t;
+  t.path = FwdTile::OWN;
+  if (!g->separable) {
+    st = trial(t);
+  } else if (rows_of(g, d_vol, vol_dtype, t)) {
     for (int vg : {8, 16, 1}) {
-      if (!g->separable && (k != 6 || vg != 8)) continue;
-      FwdTile t;
+      t.view_group = vg;
+      if (st == GJP_OK) st = trial(t);
+    }
+  }
+  t.path = FwdTile::TILES;
+  for (int k : {8, 7, 6, 5, 4}) {
+    if (k == 7 && !pairs) continue;
+    for (int vg : {8, 16, 1}) {
       t.tile_v_log2 = k;
       t.view_group = vg;
       t.ru_group = 4;
-      st = trial(t);
-      if (st != GJP_OK) break;
+      if (st == GJP_OK) st = trial(t);
     }
-    if (st != GJP_OK) break;
   }
-  if (st == GJP_OK && !rows && g->separable) {
-    FwdTile t = best;
+  if (st == GJP_OK && best.path == FwdTile::TILES) {
+    t = best;
     t.ru_group = 2;
     st = trial(t);
   }
@@ -1117,6 +1177,10 @@ extern "C" gjp_status gjp_autotune_forward(const gjp_geometry* g, const void* d_
   (void)hipEventDestroy(e1);
   if (st != GJP_OK) return st;
   {
+    FwdTile rule = best;  // the default's kernels: no need to name them
+    rule.path = FwdTile::BY_RULE;
+    const bool own = g->separable ? rows_of(g, d_vol, vol_dtype, rule) != 0 : deals_tiles(g, rule);
+    if (own == (best.path == FwdTile::OWN)) best = rule;
     const std::string key = tune_key(g, vol_dtype);
     const std::string dev = tune_cache_path() ? device_tag() : std::string();
     std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -1364,7 +1428,8 @@ std::string plan_key(int n, const gjp_geometry* const* g, const void* const* d_v
   for (int i = 0; i < n; ++i) {
     k += "|" + std::to_string(g[i]->id) + ":" + std::to_string(dtypes[i]);
     const FwdTile t = tile_for(g[i], dtypes[i]);
-    k += ":" + std::to_string(t.tile_v_log2) + ":" + std::to_string(rows_of(g[i], d_vols[i], dtypes[i]));
+    k += ":" + std::to_string(t.tile_v_log2) + ":" +
+         std::to_string(rows_of(g[i], d_vols[i], dtypes[i], t));
   }
   return k;
 }
@@ -1434,7 +1499,7 @@ gjp_status build_plan(int n, const gjp_geometry* const* g, const void* const* d_
     if (!block_fits_32bit(g[i]->n, dtypes[i]))
       return fail(GJP_EUNSUPPORTED, "batched: volume planes too large for 32-bit block offsets");
     pad_off[i] = pad_bytes;
-    if (!rows_of(g[i], d_vols[i], dtypes[i]))
+    if (!rows_of(g[i], d_vols[i], dtypes[i], tile_for(g[i], dtypes[i])))
       pad_bytes += (size_t)(2 * copy_bytes(g[i]->n, dtypes[i]));
   }
   if (pad_bytes) GJP_HIP(hipMalloc(&P->padded_all, pad_bytes), "batched: padded volumes");
@@ -1452,7 +1517,7 @@ gjp_status build_plan(int n, const gjp_geometry* const* g, const void* const* d_
     // the batched launch runs the tuned tile with one or three rays per lane;
     // a tuned two-rays-per-lane tile becomes the one-ray tile (same sums)
     if (t2.tile_v_log2 == 7) t2.tile_v_log2 = 6;
-    fill_fwd_args(g[i], d_views, rows_of(g[i], d_vols[i], dtypes[i]), nullptr, t2, I.a);
+    fill_fwd_args(g[i], d_views, rows_of(g[i], d_vols[i], dtypes[i], tile), nullptr, t2, I.a);
     if (!I.a.rows) {
       I.padded = static_cast<char*>(P->padded_all) + pad_off[i];
       set_padded(I.a, I.padded, dtypes[i], g[i]->n);

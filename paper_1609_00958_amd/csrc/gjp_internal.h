@@ -28,9 +28,14 @@ struct gjp_geometry {
   // the rays of a detector column share their in-plane coefficients, and the
   // adjoint uses the column-form gather.
   bool separable = false;
-  // Rays per lane of the row forward (gjp_forward_rows.hip); 0: the forward
-  // runs on padded pair copies.
+  // Rays per lane of the row forward (gjp_forward_rows.hip); 0: it cannot take the
+  // geometry. rows_pay: it is the default (else the padded copies are).
   int rows = 0;
+  bool rows_pay = false;
+  // General geometries: tile_v_log2 of the dealt tiles (FwdArgs::spread); deal: they are
+  // the default (else groups of views with the set tile are).
+  int deal_tile = 4;
+  bool deal = false;
   bool free_gather = false;  // general geometry that adj_free_kernel takes
   // The adjoint runs as launch_adjoint_tiles, whose tiles of 64 and 128 voxels
   // along axis 2 need at most tile_rows[0] and tile_rows[1] detector rows.
@@ -104,6 +109,9 @@ struct FwdTile {
   int remap = 1;        // 1: contiguous tile ranges per XCD
   int view_group = 8;   // consecutive views that share each tile's turn
   int ru_group = 4;     // planes whose wide loads a lane issues together (2 or 4)
+  int path = BY_RULE;   // kernels of the geometry's own (row forward, dealt tiles) or
+                        // the padded copies in groups of views, with the tile above
+  enum { BY_RULE, OWN, TILES };
 };
 
 // Arguments of one forward launch (one volume, a range of views).

@@ -194,11 +194,20 @@ __global__ __launch_bounds__(256) void pad_kernel(const E* __restrict__ src, E* 
 // Forward projection of one ray (Algorithm 1).
 // ---------------------------------------------------------------------------
 
+// Planes whose loads a lane of the per-lane loops issues together. The tile kernels take
+// two (axis 2: one), which keeps their registers, and so their occupancy, for the
+// row-uniform loop; the kernel of dealt tiles (GRP 0) takes four.
+template <int GRP>
+struct Together {
+  static constexpr int buf = GRP == 0 ? 4 : 2, axis2 = GRP == 0 ? 4 : 1;
+  static constexpr int uniform = GRP == 0 ? 4 : GRP;
+};
+
 // Sampling loop for driving axes 0 and 1 with 32-bit offsets from copy A
-// (copy B follows it; both below 4 GiB together), four samples per iteration so
-// that four wide loads are in flight per lane. The lanes of a wavefront may
+// (copy B follows it; both below 4 GiB together), NP samples per iteration so
+// that NP wide loads are in flight per lane. The lanes of a wavefront may
 // differ in m, so the copy is chosen by offset, not by resource.
-template <typename T, int WF>
+template <typename T, int WF, int NP>
 __device__ __forceinline__ float fwd_loop_buf(const FwdArgs& a, const RaySetup& R) {
   constexpr uint32_t pe = 2 * sizeof(T);
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -211,26 +220,54 @@ __device__ __forceinline__ float fwd_loop_buf(const FwdArgs& a, const RaySetup& 
   uint32_t off_m = (R.m == 0 ? 0u : (uint32_t)a.copy_bytes) + (uint32_t)(R.i0 + 1) * Sm +
                    (uint32_t)Sa + pe;
   float acc = 0.0f;
-  // (the loads of four planes together; after the ray's last: its last again, not
-  // added)
-  for (int i = R.i0; i < R.i1; i += 4) {
-    Quad q[4];
-    float wfa[4], wca[4], wfb[4], wcb[4];
+  if constexpr (NP > 2) {
+    // (after the ray's last plane: its last again, not added)
+    for (int i = R.i0; i < R.i1; i += NP) {
+      Quad q[NP];
+      float wfa[NP], wca[NP], wfb[NP], wcb[NP];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int d = min(k, R.i1 - 1 - i);
-      int ia, ib;
-      sample_axis<WF>((float)(i + d), R.ga, R.ca, hia, ia, wfa[k], wca[k]);
-      sample_axis<WF>((float)(i + d), R.gb, R.cb, hib, ib, wfb[k], wcb[k]);
-      const uint32_t o = (uint32_t)__mul24(ia, Sa) + off_m + (uint32_t)d * Sm + (uint32_t)ib * pe;
-      q[k] = buf_quad(rs, o, 0, (const T*)nullptr);
-    }
+      for (int k = 0; k < NP; ++k) {
+        const int d = min(k, R.i1 - 1 - i);
+        int ia, ib;
+        sample_axis<WF>((float)(i + d), R.ga, R.ca, hia, ia, wfa[k], wca[k]);
+        sample_axis<WF>((float)(i + d), R.gb, R.cb, hib, ib, wfb[k], wcb[k]);
+        const uint32_t o = (uint32_t)__mul24(ia, Sa) + off_m + (uint32_t)d * Sm + (uint32_t)ib * pe;
+        q[k] = buf_quad(rs, o, 0, (const T*)nullptr);
+      }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float sum = accumulate4(acc, wfa[k], wca[k], wfb[k], wcb[k], q[k]);
-      acc = i + k < R.i1 ? sum : acc;
+      for (int k = 0; k < NP; ++k) {
+        const float sum = accumulate4(acc, wfa[k], wca[k], wfb[k], wcb[k], q[k]);
+        acc = i + k < R.i1 ? sum : acc;
+      }
+      off_m += NP * Sm;
     }
-    off_m += 4 * Sm;
+  } else {
+    float fi = (float)R.i0;
+    int i = R.i0;
+    for (; i + 1 < R.i1; i += 2) {
+      int ia0, ib0, ia1, ib1;
+      float wfa0, wca0, wfb0, wcb0, wfa1, wca1, wfb1, wcb1;
+      sample_axis<WF>(fi, R.ga, R.ca, hia, ia0, wfa0, wca0);
+      sample_axis<WF>(fi, R.gb, R.cb, hib, ib0, wfb0, wcb0);
+      sample_axis<WF>(fi + 1.0f, R.ga, R.ca, hia, ia1, wfa1, wca1);
+      sample_axis<WF>(fi + 1.0f, R.gb, R.cb, hib, ib1, wfb1, wcb1);
+      const uint32_t o0 = (uint32_t)__mul24(ia0, Sa) + off_m + (uint32_t)ib0 * pe;
+      const uint32_t o1 = (uint32_t)__mul24(ia1, Sa) + off_m + Sm + (uint32_t)ib1 * pe;
+      const Quad q0 = buf_quad(rs, o0, 0, (const T*)nullptr);
+      const Quad q1 = buf_quad(rs, o1, 0, (const T*)nullptr);
+      acc = accumulate4(acc, wfa0, wca0, wfb0, wcb0, q0);
+      acc = accumulate4(acc, wfa1, wca1, wfb1, wcb1, q1);
+      fi += 2.0f;
+      off_m += 2 * Sm;
+    }
+    if (i < R.i1) {
+      int ia0, ib0;
+      float wfa0, wca0, wfb0, wcb0;
+      sample_axis<WF>(fi, R.ga, R.ca, hia, ia0, wfa0, wca0);
+      sample_axis<WF>(fi, R.gb, R.cb, hib, ib0, wfb0, wcb0);
+      const uint32_t o0 = (uint32_t)__mul24(ia0, Sa) + off_m + (uint32_t)ib0 * pe;
+      acc = accumulate4(acc, wfa0, wca0, wfb0, wcb0, buf_quad(rs, o0, 0, (const T*)nullptr));
+    }
   }
   return acc;
 }
@@ -395,11 +432,12 @@ __device__ __forceinline__ float fwd_sum(const FwdArgs& a, const RaySetup& R) {
     const int hi = __builtin_amdgcn_readfirstlane(wave_max(has ? R.i1 : -1));
     const int mid_lo = __builtin_amdgcn_readfirstlane(wave_max(has ? R.i0 : -1));
     const int mid_hi = __builtin_amdgcn_readfirstlane(wave_min(has ? R.i1 : 0x7fffffff));
-    acc = fwd_loop_rowuniform<T, WF, GRP>(a, R, lm, lca, lga, lo, hi, mid_lo, mid_hi);
+    acc = fwd_loop_rowuniform<T, WF, Together<GRP>::uniform>(a, R, lm, lca, lga, lo, hi, mid_lo,
+                                                             mid_hi);
     if (!has) acc = 0.0f;
   } else if (R.m != 2) {
     if constexpr (!IDX64)
-      acc = fwd_loop_buf<T, WF>(a, R);
+      acc = fwd_loop_buf<T, WF, Together<GRP>::buf>(a, R);
     else
       acc = fwd_loop_ptr<T, WF>(a, R);
   } else {
@@ -408,25 +446,41 @@ __device__ __forceinline__ float fwd_sum(const FwdArgs& a, const RaySetup& R) {
     const T* base = static_cast<const T*>(a.vol_a);
     const long long S0 = a.S0, S1 = a.S1;
     const float hia = a.G.hi[0], hib = a.G.hi[1];
-    // (the loads of four planes together; after the ray's last: its last again,
-    // not added)
-    for (int i = R.i0; i < R.i1; i += 4) {
-      Quad q[4];
-      float wfa[4], wca[4], wfb[4], wcb[4];
+    if constexpr (Together<GRP>::axis2 > 1) {
+      constexpr int NP = Together<GRP>::axis2;
+      // (after the ray's last plane: its last again, not added)
+      for (int i = R.i0; i < R.i1; i += NP) {
+        Quad q[NP];
+        float wfa[NP], wca[NP], wfb[NP], wcb[NP];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int ik = min(i + k, R.i1 - 1);
-        int ia, ib;
-        sample_axis<WF>((float)ik, R.ga, R.ca, hia, ia, wfa[k], wca[k]);
-        sample_axis<WF>((float)ik, R.gb, R.cb, hib, ib, wfb[k], wcb[k]);
-        const long long e = (long long)(ia + 1) * S0 + (long long)(ib + 1) * S1 + (ik + 1);
-        ptr_pair(base + 2 * e, q[k].a0z0, q[k].a0z1);
-        ptr_pair(base + 2 * (e + S0), q[k].a1z0, q[k].a1z1);
+        for (int k = 0; k < NP; ++k) {
+          const int ik = min(i + k, R.i1 - 1);
+          int ia, ib;
+          sample_axis<WF>((float)ik, R.ga, R.ca, hia, ia, wfa[k], wca[k]);
+          sample_axis<WF>((float)ik, R.gb, R.cb, hib, ib, wfb[k], wcb[k]);
+          const long long e = (long long)(ia + 1) * S0 + (long long)(ib + 1) * S1 + (ik + 1);
+          ptr_pair(base + 2 * e, q[k].a0z0, q[k].a0z1);
+          ptr_pair(base + 2 * (e + S0), q[k].a1z0, q[k].a1z1);
+        }
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+          const float sum = accumulate4(acc, wfa[k], wca[k], wfb[k], wcb[k], q[k]);
+          acc = i + k < R.i1 ? sum : acc;
+        }
       }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float sum = accumulate4(acc, wfa[k], wca[k], wfb[k], wcb[k], q[k]);
-        acc = i + k < R.i1 ? sum : acc;
+    } else {
+      float fi = (float)R.i0;
+      for (int i = R.i0; i < R.i1; ++i) {
+        int ia, ib;
+        float wfa, wca, wfb, wcb;
+        sample_axis<WF>(fi, R.ga, R.ca, hia, ia, wfa, wca);
+        sample_axis<WF>(fi, R.gb, R.cb, hib, ib, wfb, wcb);
+        const long long e = (long long)(ia + 1) * S0 + (long long)(ib + 1) * S1 + (i + 1);
+        Quad q;
+        ptr_pair(base + 2 * e, q.a0z0, q.a0z1);
+        ptr_pair(base + 2 * (e + S0), q.a1z0, q.a1z1);
+        acc = accumulate4(acc, wfa, wca, wfb, wcb, q);
+        fi += 1.0f;
       }
     }
   }
@@ -1039,34 +1093,32 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs& a, int view, int t) {
 // volume reads in L2 instead of each view streaming the volume again.
 template <typename T, int WF, bool IDX64, int GRP, int RPL>
 __device__ __forceinline__ void fwd_block(const FwdArgs& a) {
-  int view, tile;
-  if (a.spread) {
-    // general geometries: see FwdArgs::spread
-    const uint32_t per_xcd = (uint32_t)a.tiles_per_view / 8, k = blockIdx.x / 8;
-    view = (int)(k / per_xcd);
-    const uint32_t r = k - (uint32_t)view * per_xcd, unit = (uint32_t)a.spread, uc = r / unit;
-    const uint32_t t = (8 * uc + (blockIdx.x + (uint32_t)view) % 8) * unit + (r - uc * unit);
-    const uint32_t tu = t / (uint32_t)a.tiles_v, tv = t - tu * (uint32_t)a.tiles_v;
-    if (tu >= (uint32_t)a.tiles_u) return;
-    tile = (int)(tv * (uint32_t)a.tiles_u + tu);
-  } else {
-    uint32_t b = blockIdx.x;
-    if (a.remap) b = xcd_remap(b, gridDim.x);
-    const uint32_t K = (uint32_t)a.view_group, tpv = (uint32_t)a.tiles_per_view;
-    const uint32_t grp = b / (K * tpv);
-    const uint32_t r = b - grp * K * tpv;
-    const uint32_t v0 = grp * K;
-    const uint32_t kg = min(K, (uint32_t)a.n_views - v0);  // views in this group
-    const uint32_t t = r / kg;
-    view = (int)(v0 + (r - t * kg));
-    tile = (int)t;
-  }
-  fwd_tile<T, WF, IDX64, GRP, RPL>(a, view, tile);
+  uint32_t b = blockIdx.x;
+  if (a.remap) b = xcd_remap(b, gridDim.x);
+  const uint32_t K = (uint32_t)a.view_group, tpv = (uint32_t)a.tiles_per_view;
+  const uint32_t grp = b / (K * tpv);
+  const uint32_t r = b - grp * K * tpv;
+  const uint32_t v0 = grp * K;
+  const uint32_t kg = min(K, (uint32_t)a.n_views - v0);  // views in this group
+  const uint32_t t = r / kg;
+  fwd_tile<T, WF, IDX64, GRP, RPL>(a, (int)(v0 + (r - t * kg)), (int)t);
 }
 
 template <typename T, int WF, bool IDX64, int GRP>
 __global__ __launch_bounds__(256) void fwd_kernel(const FwdArgs a) {
   fwd_block<T, WF, IDX64, GRP, 1>(a);
+}
+
+// Tiles dealt to the XCDs (FwdArgs::spread).
+template <typename T, int WF, bool IDX64>
+__global__ __launch_bounds__(256) void fwd_spread_kernel(const FwdArgs a) {
+  const uint32_t per_xcd = (uint32_t)a.tiles_per_view / 8, k = blockIdx.x / 8;
+  const uint32_t view = k / per_xcd;
+  const uint32_t r = k - view * per_xcd, unit = (uint32_t)a.spread, uc = r / unit;
+  const uint32_t t = (8 * uc + (blockIdx.x + view) % 8) * unit + (r - uc * unit);
+  const uint32_t tu = t / (uint32_t)a.tiles_v, tv = t - tu * (uint32_t)a.tiles_v;
+  if (tu >= (uint32_t)a.tiles_u) return;
+  fwd_tile<T, WF, IDX64, 0, 1>(a, (int)view, (int)(tv * (uint32_t)a.tiles_u + tu));
 }
 
 // Two rays per lane (16-bit storage, 128-wide tiles).
@@ -2093,6 +2145,13 @@ int launch_pad(const void* src, void* copy_a, void* copy_b, int dtype, const int
 // which the one-ray tiles should not pay in occupancy.
 template <typename T, int WF>
 static void launch_fwd_t(const FwdArgs& a, bool idx64, unsigned grid, hipStream_t s) {
+  if (a.spread) {
+    if (idx64)
+      fwd_spread_kernel<T, WF, true><<<grid, 256, 0, s>>>(a);
+    else
+      fwd_spread_kernel<T, WF, false><<<grid, 256, 0, s>>>(a);
+    return;
+  }
   if (a.tile_v_log2 == 8) {
     GJP_FWD_LAUNCH(fwd_triple_kernel);
     return;

@@ -43,6 +43,9 @@ SHORT = (
     ("fwd_triple_kernel<gjp::f16_t", "forward_f16_triples"),
     ("batched_fwd_kernel", "batched"),
     ("batched_pad_kernel", "batched_pad"),
+    ("fwd_spread_kernel<float", "forward_f32"),
+    ("fwd_spread_kernel<gjp::bf16_t", "forward_bf16"),
+    ("fwd_spread_kernel<gjp::f16_t", "forward_f16"),
     ("fwd_kernel<float", "forward_f32"),
     ("fwd_kernel<gjp::bf16_t", "forward_bf16"),
     ("fwd_kernel<gjp::f16_t", "forward_f16"),

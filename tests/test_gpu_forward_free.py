@@ -33,3 +33,56 @@ def test_tiles(oracle_mod, beam, shape, n_views, n_u, n_v):
     y = gjp.forward(d, G)
     assert_parity(y.cpu().numpy(), oracle_mod.forward(og, x), TOL32)
     assert torch.equal(gjp.forward_batched([d], [G])[0], y)
+
+
+@pytest.mark.parametrize("n_u,n_v,n_views", [(1, 70, 3), (3, 200, 5), (4, 64, 9), (5, 130, 2), (8, 33, 4),
+                                             (12, 90, 3), (40, 1, 30), (40, 2, 3), (300, 3, 30),
+                                             (60, 15, 5)])
+@pytest.mark.parametrize("beam", ["cone", "parallel"])
+def test_narrow_detectors(oracle_mod, beam, n_u, n_v, n_views):
+    """Few columns or rows: dealt tiles of every shape, and groups of views."""
+    import torch
+
+    import paper_1609_00958_amd as gjp
+    shape = (19, 24, 17)
+    make = workloads.random_cone_views if beam == "cone" else workloads.random_parallel_views
+    G = gjp.Geometry(shape, make(43, n_views, shape, n_u, n_v), n_u, n_v, beam=beam)
+    og = oracle_mod.Geometry(G.shape, G.views, n_u, n_v,
+                             beam=oracle_mod.CONE if beam == "cone" else oracle_mod.PARALLEL)
+    x = np.random.default_rng(44).uniform(0, 1, size=shape).astype(np.float32)
+    note(f"general forward {beam} {n_views} x {n_u} x {n_v}")
+    d = torch.from_numpy(x).to(cuda())
+    y = gjp.forward(d, G)
+    assert_parity(y.cpu().numpy(), oracle_mod.forward(og, x), TOL32)
+    assert torch.equal(gjp.forward_batched([d], [G])[0], y)
+
+
+@pytest.mark.parametrize("kind", ["column scan", "wide cone", "general"])
+@pytest.mark.parametrize("dtype", ["float32", "float16"])
+def test_autotuned_choice(oracle_mod, tmp_path, monkeypatch, kind, dtype):
+    """Whichever kernels the autotuner chooses: the forward within the bound, batches
+    bitwise equal to single calls, and the choice read back from the file."""
+    import torch
+
+    import paper_1609_00958_amd as gjp
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("GJP_TUNE_CACHE", str(path))
+    shape, n_u, n_v = (24, 22, 30), 33, 30
+    if kind == "general":
+        G = gjp.Geometry(shape, workloads.random_cone_views(45, 7, shape, n_u, n_v), n_u, n_v)
+    else:
+        sod = 300.0 if kind == "column scan" else 26.0
+        G = gjp.Geometry.circular_cone(shape, 7, n_u, n_v, sod, sod + 20.0, 1.1, 1.7)
+    og = oracle_mod.Geometry(G.shape, G.views, n_u, n_v, beam=oracle_mod.CONE)
+    x = torch.from_numpy(np.random.default_rng(46).uniform(0, 1, size=shape).astype(np.float32))
+    x = x.to(getattr(torch, dtype))
+    note(f"autotuned {kind} {dtype}")
+    d = x.to(cuda())
+    gjp.autotune(d, G)
+    y = gjp.forward(d, G)
+    assert_parity(y.cpu().numpy(), oracle_mod.forward(og, x.float().numpy()), TOL32)
+    assert torch.equal(gjp.forward_batched([d], [G])[0], y)
+    gjp.reset_forward_tile(G, getattr(torch, dtype))  # the file's entry applies
+    assert torch.equal(gjp.forward(d, G), y)
+    for entry in path.read_text().splitlines():
+        assert len(entry.split()) in (5, 6)
