@@ -477,17 +477,18 @@ static bool deals_tiles_by_rule(const gjp_geometry& g, int& tile) {
   return tiles <= (g.n_u < 16 ? 256.0 : 512.0) || tiles * std::max(pu, pv) >= 950.0;
 }
 
-// Rays per lane of the row forward (gjp_forward_rows.hip), or 0 where the padded
-// copies are sampled instead: not a column geometry, rays so far apart that 128
-// of them span more than the window, or too few rays in a column to share its
-// rows. The costs are times per column and plane as measured at 256^3, 360 views
-// of 384 columns (1 = 1 ms in all): a wavefront of 64 r rays 1.81, 2.05, 2.25
-// and 3.26 for r = 2, 3, 4 and 6 (with voxels of a second load: +0.5), a
-// wavefront of the copies' kernel 0.92 per 64 rays; their two copies take 14 us
-// and 6.5 ps per voxel. 64^3, 64 x 64 rays: 22 against 31 us for 64 views, 93
-// against 64 us for 360.
-static int rows_per_lane(const gjp_geometry& g, bool& pay) {
-  pay = false;
+// Rays per lane of the row forward (gjp_forward_rows.hip), or 0 where it cannot take the
+// geometry: not a column geometry, or rays so far apart that 128 of them span more than
+// the window. pay: it is the default; else there are too few rays in a column to share
+// its rows, and the padded copies are sampled. The costs are times per column and plane
+// as measured at 256^3, 360 views of 384 columns (1 = 1 ms in all): a wavefront of 64 r
+// rays 1.81, 2.05, 2.25 and 3.26 for r = 2, 3, 4 and 6 (with voxels of a second load:
+// +0.5; 16-bit volumes a tenth more), a wavefront of the copies' kernel 0.92 per 64 rays;
+// their two copies take 14 us and 6.5 ps per voxel. 64^3, 64 x 64 rays: 22 against 31 us
+// for 64 views, 93 against 64 us for 360. 16-bit copies that fit the L2s: 0.83 (128^3, 200
+// views of 192 x 128 307 us against 286; 256^3, 100 views of 384 x 128 657 against 726).
+static int rows_per_lane(const gjp_geometry& g, bool pay[2]) {
+  pay[0] = pay[1] = false;
   if (!g.separable) return 0;
   const double s0 = (double)g.n[1] * g.n[2] * 4.0, s1 = (double)g.n[2] * 4.0;
   if (66.0 * (s0 + s1) >= 2147483648.0) return 0;  // 31-bit offsets within 64 planes
@@ -508,8 +509,11 @@ static int rows_per_lane(const gjp_geometry& g, bool& pay) {
   }
   const double planes = (double)std::max(g.n[0], g.n[1]) * g.n_u * g.n_views;
   const double voxels = (double)g.n[0] * g.n[1] * g.n[2];
-  pay = best > 0 &&
-        28.0e-12 * planes * (best_cost - 0.92 * ceil(g.n_v / 64.0)) <= 14.0e-6 + 6.5e-12 * voxels;
+  if (best == 0) return 0;
+  const double waves = ceil(g.n_v / 64.0), l2 = 32.0 * 1024 * 1024;
+  pay[0] = 28.0e-12 * planes * (best_cost - 0.92 * waves) <= 14.0e-6 + 6.5e-12 * voxels;
+  pay[1] = 28.0e-12 * planes * (1.1 * best_cost - (4.0 * voxels <= l2 ? 0.83 : 1.17) * waves) <=
+           14.0e-6 + 4.0e-12 * voxels;
   return best;
 }
 
@@ -932,7 +936,7 @@ long long padded_elems(const int* n) {
 // 16-bit rows that do not all start on 4 bytes would have to be read element by
 // element: 81 us instead of 42 for FP16 97 x 83 x 121 and 45 views of 129 x 101.
 int rows_of(const gjp_geometry* g, const void* d_vol, int dtype, const FwdTile& tile) {
-  if (tile.path == FwdTile::BY_RULE ? !g->rows_pay : tile.path == FwdTile::TILES) return 0;
+  if (tile.path == FwdTile::BY_RULE ? !g->rows_pay[dtype != GJP_F32] : tile.path == FwdTile::TILES) return 0;
   return dtype == GJP_F32 || (g->n[2] % 2 == 0 && (uintptr_t)d_vol % 4 == 0) ? g->rows : 0;
 }
 

@@ -406,7 +406,19 @@ static int dispatch_main() {
   CHECK(gjp_views_circular_cone(30, 256, 512, 2, 2, 64, 64, v.data()) == GJP_OK);
   g = make(n, GJP_CONE, 30, 64, 64, v.data());  // ordinary circular scan
   CHECK(g && g->separable && g->rows > 0 && g->tiles && !g->free_gather);
+  CHECK(g->rows_pay[0] && g->rows_pay[1]);
   gjp_destroy_geometry(g);
+  {  // columns of 128 rays: rows for FP32, small 16-bit copies for 16 bits; 64: copies
+    const int m[3] = {128, 128, 128};
+    std::vector<double> w(12 * 200);
+    for (int n_v : {64, 128, 192}) {
+      CHECK(gjp_views_circular_cone(200, 512, 768, 1.0, 1.55 * 128 / n_v, 192, n_v, w.data()) ==
+            GJP_OK);
+      g = make(m, GJP_CONE, 200, 192, n_v, w.data());
+      CHECK(g && g->rows > 0 && g->rows_pay[0] == (n_v > 64) && g->rows_pay[1] == (n_v > 128));
+      gjp_destroy_geometry(g);
+    }
+  }
   CHECK(gjp_views_parallel(30, 1, 1, 90, 80, v.data()) == GJP_OK);
   g = make(n, GJP_PARALLEL, 30, 90, 80, v.data());
   CHECK(g && g->separable && g->rows > 0 && g->tiles && !g->free_gather);
@@ -419,6 +431,15 @@ static int dispatch_main() {
   for (int k = 0; k < 30; ++k) v[12 * k + 9] = 0.3;  // tilted detectors
   g = make(n, GJP_CONE, 30, 64, 64, v.data());
   CHECK(g && !g->separable && !g->rows && !g->tiles && g->free_gather);
+  gjp_destroy_geometry(g);
+  CHECK(gjp_views_circular_cone(30, 44, 80, 2, 1.5, 64, 90, v.data()) == GJP_OK);
+  g = make(n, GJP_CONE, 30, 64, 90, v.data());  // columns along axis 2, some rays driven by it
+  CHECK(g && !g->separable && !g->deal);
+  gjp_destroy_geometry(g);
+  CHECK(gjp_views_circular_cone(30, 256, 512, 2, 2, 64, 64, v.data()) == GJP_OK);
+  for (int k = 0; k < 30; ++k) v[12 * k + 9] = 0.3;
+  g = make(n, GJP_CONE, 30, 64, 64, v.data());
+  CHECK(g && g->deal && g->deal_tile == 4);
   gjp_destroy_geometry(g);
   for (int k = 0; k < 30; ++k)  // and sources inside the grid
     for (int j = 0; j < 3; ++j) v[12 * k + j] *= 0.05;
