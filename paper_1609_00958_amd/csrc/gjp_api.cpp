@@ -276,6 +276,36 @@ static void detector_projection(const double* v, int beam, float* P) {
   for (int k = 0; k < 12; ++k) P[k] = (float)R[k];
 }
 
+// Columns of a cone view (grid units) that decide what holds for all of them: the
+// directions r_0, r_1 and the axis-2 components z of the first and last row are linear in
+// the column, so the driving axis and every largest or smallest |r| or |z| or maximum of
+// two of them changes its course only where one of them or a sum or difference of two
+// is zero. The integers around those, and the ends; all columns if they are few. Returns
+// their number.
+constexpr int kMaxCandidates = 48;
+static int column_candidates(const double* o, int n_u, int n_v, int* out) {
+  int n = 0;
+  if (n_u <= kMaxCandidates) {
+    for (; n < n_u; ++n) out[n] = n;
+    return n;
+  }
+  const double zv = (double)(n_v - 1) * o[11];
+  // value at column 0 and step per column
+  const double r0 = o[3] - o[0], r1 = o[4] - o[1], z0 = o[5] - o[2], z1 = z0 + zv;
+  const double line[7][2] = {{r0, o[6]}, {r1, o[7]}, {r0 - r1, o[6] - o[7]}, {r0 + r1, o[6] + o[7]},
+                             {z0, o[8]}, {z1, o[8]}, {z0 + z1, 2.0 * o[8]}};
+  out[n++] = 0;
+  out[n++] = n_u - 1;
+  for (const auto& l : line) {
+    const double at = -l[0] / l[1];
+    if (!(at > -4.0 && at < n_u + 3.0)) continue;  // (also no step: not a number)
+    const int c = (int)floor(at);
+    for (int k = c - 2; k <= c + 3; ++k)
+      if (k > 0 && k < n_u - 1) out[n++] = k;
+  }
+  return n;
+}
+
 // True when, in every view, dv has no component on axes 0 and 1 and no ray is
 // driven by axis 2 (|r_2| stays below max(|r_0|, |r_1|) with a safety
 // factor). Then d_0, d_1, r_0, r_1 and the source do not depend on iv, so the
@@ -289,7 +319,10 @@ static bool columns_share_inplane_setup(const gjp_geometry& g) {
       if (!(fabs(o[2]) * (1.0 + 1e-9) < fmax(fabs(o[0]), fabs(o[1])))) return false;
       continue;
     }
-    for (int iu = 0; iu < g.n_u; ++iu) {
+    int at[kMaxCandidates];
+    const int n = column_candidates(o, g.n_u, g.n_v, at);
+    for (int k = 0; k < n; ++k) {
+      const int iu = at[k];
       const double d0 = o[3] + (double)iu * o[6];
       const double d1 = o[4] + (double)iu * o[7];
       const double r0 = d0 - o[0], r1 = d1 - o[1];
@@ -331,7 +364,10 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
       if (!(w_lo > 1.0e-3 * w_hi)) return false;
       bool used[2] = {false, false};
       double r_lo[2] = {1.0e300, 1.0e300}, r_hi[2] = {-1.0e300, -1.0e300};
-      for (int iu = 0; iu < g.n_u; ++iu) {
+      int at[kMaxCandidates];
+      const int n = column_candidates(o, g.n_u, g.n_v, at);
+      for (int c = 0; c < n; ++c) {
+        const int iu = at[c];
         const double r[2] = {o[3] + (double)iu * o[6] - o[0], o[4] + (double)iu * o[7] - o[1]};
         const int m = fabs(r[1]) > fabs(r[0]) ? 1 : 0;
         used[m] = true;
@@ -391,11 +427,13 @@ static void column_spacing(const gjp_geometry& g, double& spacing, double& climb
       climb = std::max(climb, fabs(o[2]) / std::max(fabs(o[0]), fabs(o[1])));
       continue;
     }
-    // the steepest column and the farthest plane of the axes that drive one (a bound:
-    // no division per column)
+    // the steepest column and the farthest plane of the axes that drive one (a bound)
     double r_min = 1.0e300;
     bool used[2] = {false, false};
-    for (int iu = 0; iu < g.n_u; ++iu) {
+    int at[kMaxCandidates];
+    const int n = column_candidates(o, g.n_u, g.n_v, at);
+    for (int k = 0; k < n; ++k) {
+      const int iu = at[k];
       const double r0 = fabs(o[3] + (double)iu * o[6] - o[0]);
       const double r1 = fabs(o[4] + (double)iu * o[7] - o[1]);
       used[r1 > r0] = true;

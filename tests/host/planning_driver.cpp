@@ -398,6 +398,50 @@ static int scratch_main() {
   return 0;
 }
 
+// What the geometry's creation found from a few columns of each view against all of them.
+static int columns_main() {
+  int yes = 0, no = 0, tiles = 0;
+  for (int trial = 0; trial < 20000; ++trial) {
+    const int n[3] = {integer(4, 40), integer(4, 40), integer(4, 100)};
+    const int n_u = integer(40, 400), n_v = integer(2, 200);
+    const double dist = loguniform(6.0, 200.0), len = dist * uniform(1.02, 2.0);
+    double views[12];
+    column_view(GJP_CONE, uniform(0.0, 6.28), dist, uniform(-0.5, 0.5) * dist, len,
+                loguniform(0.02, 4.0), loguniform(0.02, 4.0) * (trial & 1 ? 1 : -1),
+                trial % 3 ? 0.0 : uniform(-0.5, 0.5), n_u, n_v, uniform(-0.5, 0.5) * n_v, views);
+    if (trial % 4 == 0) {  // detectors of any direction in the plane
+      const double a = uniform(-1.57, 1.57), x = cos(a) * views[6] - sin(a) * views[7],
+                   y = sin(a) * views[6] + cos(a) * views[7];
+      for (int j = 0; j < 2; ++j) views[3 + j] -= 0.5 * (n_u - 1) * ((j ? y : x) - views[6 + j]);
+      views[6] = x;
+      views[7] = y;
+    }
+    gjp_geometry* g = make(n, GJP_CONE, 1, n_u, n_v, views);
+    CHECK(g != nullptr);
+    const double* o = g->views_grid.data();
+    bool separable = o[9] == 0.0 && o[10] == 0.0;
+    bool used[2] = {false, false}, front = true;
+    for (int iu = 0; iu < n_u; ++iu) {
+      const double r[2] = {o[3] + iu * o[6] - o[0], o[4] + iu * o[7] - o[1]};
+      const double M = fmax(fabs(r[0]), fabs(r[1]));
+      const double z0 = o[5] + iu * o[8] - o[2], z1 = o[5] + iu * o[8] + (n_v - 1) * o[11] - o[2];
+      if (!(fmax(fabs(z0), fabs(z1)) * (1.0 + 1e-9) < M)) separable = false;
+      const int m = fabs(r[1]) > fabs(r[0]) ? 1 : 0;
+      used[m] = true;
+      if (!((o[m] < -3.0 && r[m] > 0.0) || (o[m] > n[m] + 20.0 && r[m] < 0.0))) front = false;
+    }
+    CHECK(g->separable == separable);
+    if (g->tiles) {
+      ++tiles;
+      CHECK(front);
+    }
+    ++(separable ? yes : no);
+    gjp_destroy_geometry(g);
+  }
+  CHECK(yes > 2000 && no > 2000 && tiles > 500);
+  return 0;
+}
+
 // The kernels that geometries of each kind are sent to.
 static int dispatch_main() {
   const int n[3] = {64, 60, 70};
@@ -455,6 +499,7 @@ int main(int argc, char** argv) {
   else if (!strcmp(what, "tiles")) tiles_main();
   else if (!strcmp(what, "scratch")) scratch_main();
   else if (!strcmp(what, "dispatch")) dispatch_main();
+  else if (!strcmp(what, "columns")) columns_main();
   else {
     fprintf(stderr, "unknown part %s\n", what);
     return 2;

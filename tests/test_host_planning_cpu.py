@@ -49,3 +49,26 @@ def test_adjoint_scratch_at_its_limits(driver):
 
 def test_dispatch(driver):
     assert "dispatch: ok" in _run([driver, "dispatch"])
+
+
+def test_geometry_rules_look_at_the_columns_that_decide(driver):
+    assert "columns: ok" in _run([driver, "columns"])
+
+
+def test_geometry_creation_does_not_grow_with_the_columns():
+    """720 views: sixteen times the columns at no more than four times the time (each
+    view's rules look at a few columns; reading all of them grew sixteenfold)."""
+    import time
+
+    import paper_1609_00958_amd as gjp
+
+    def best(n_u):
+        v = gjp.views_circular_cone(720, 2048.0, 3072.0, 0.01, 1.0, n_u, 64)
+        t = []
+        for _ in range(9):
+            t0 = time.perf_counter()
+            gjp.Geometry((64, 64, 64), v, n_u, 64)
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    assert best(32000) < 4 * best(2000)
