@@ -19,7 +19,7 @@
 // A workgroup owns P planes; per view the detector window they need (columns u,
 // rows v of the sinogram scaled by the rays' step lengths) is copied to LDS once
 // and shared. The columns driven by axis 0 and by axis 1 are two launches, the
-// second adding to the first's volume. For volumes whose tiles alone do not
+// second adding to the first's volume (one if the views have one of them only). For volumes whose tiles alone do not
 // fill the device both axes and several splits of the views run as one launch
 // into partial volumes, summed by a second kernel.
 #include <hip/hip_runtime.h>
@@ -57,8 +57,9 @@ struct TileArgs {
   size_t slice;
   int n_views, n_u, n_v;
   int m0;              // driving axis of slice 0; odd slices take the other one
+  int both;            // 0: every slice takes m0
   int accumulate;      // add to vol (else overwrite it)
-  int splits;          // slices 2 k and 2 k + 1: views k, k + splits, ...
+  int splits;          // slices 2 k and 2 k + 1 (both = 0: k): views k, k + splits, ...
   int nzb;             // tiles along axis 2
 };
 
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(P * 64) __attribute__((amdgpu_waves_per_eu(8))) voi
   const int pl = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   Slot* slot = s_slot[pl];
   const int slice = blockIdx.y;
-  const int m = a.m0 ^ (slice & 1);
+  const int m = a.m0 ^ (slice & a.both);
 
   // tile of this workgroup: XCDs walk contiguous ranges; within a block of
   // axis-2 tiles, strips of 8 tiles along the rows, so that the workgroups
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(P * 64) __attribute__((amdgpu_waves_per_eu(8))) voi
 
   const bool cone = a.G.beam == BEAM_CONE;
   // this slice's views: v0, v0 + splits, ...
-  const int sv0 = slice >> 1, ngv = (a.n_views - sv0 + a.splits - 1) / a.splits;
+  const int sv0 = slice >> a.both, ngv = (a.n_views - sv0 + a.splits - 1) / a.splits;
   bool store = a.accumulate == 0;
 
   for (int batch = 0; batch < ngv; batch += kViews) {
@@ -255,6 +256,7 @@ __global__ __launch_bounds__(P * 64) __attribute__((amdgpu_waves_per_eu(8))) voi
     }
     __syncthreads();
     uint64_t vmask = uniform64(s_mask);
+    const bool some = vmask != 0;
 
     // chunk of columns being worked on, and the one after it
     struct Chunk {
@@ -454,9 +456,10 @@ __global__ __launch_bounds__(P * 64) __attribute__((amdgpu_waves_per_eu(8))) voi
 
     // Add the accumulators to the volume (or store them) and clear them:
     // partial sums of at most kViews views keep the rounding error of long sums
-    // down.
+    // down. (Nothing to add where no view has rays on the tile: half of a launch whose
+    // few views the other axis drives.)
     const int plane = pm0 + pl;
-    if (plane < nm) {
+    if (plane < nm && (store || some)) {
       const int z = zt + here(tid) * ZL, ra0 = tr * R;
       const size_t sr = m == 0 ? (size_t)n2 : (size_t)a.G.n[1] * n2;
       const size_t sp = m == 0 ? (size_t)a.G.n[1] * n2 : (size_t)n2;
@@ -525,7 +528,7 @@ static int run_tiles(const gjp_geometry* g, TileArgs& a, int slices, hipStream_t
   a.nzb = (g->n[2] + 64 * ZL - 1) / (64 * ZL);
   unsigned long long nwg = 0;
   for (int m = 0; m < 2; ++m) {
-    if (slices == 1 && m != a.m0) continue;
+    if (!a.both && m != a.m0) continue;
     const unsigned long long t = (unsigned long long)((g->n[m] + P - 1) / P) *
                                  ((g->n[1 - m] + R - 1) / R) * a.nzb;
     if (t > nwg) nwg = t;
@@ -555,8 +558,8 @@ int launch_adjoint_scale(const gjp_geometry* g, const double* views, const float
 }
 
 int launch_adjoint_tiles(const gjp_geometry* g, const double* views, const float* proj,
-                         const float* rays, int n_views, bool accumulate, float* vol, float* part,
-                         int splits, hipStream_t s) {
+                         const float* rays, int n_views, int axes, bool accumulate, float* vol,
+                         float* part, int splits, hipStream_t s) {
   TileArgs a;
   a.G = g->gg;
   a.views = views;
@@ -567,23 +570,30 @@ int launch_adjoint_tiles(const gjp_geometry* g, const double* views, const float
   a.n_views = n_views;
   a.n_u = g->n_u;
   a.n_v = g->n_v;
-  a.m0 = 0;
-  a.accumulate = accumulate && !part ? 1 : 0;
-  a.splits = part ? splits : 1;
+  a.accumulate = accumulate ? 1 : 0;
+  a.splits = 1;
+  a.both = 0;
   // two voxels per lane unless one wavefront's 64 cover axis 2 (64 voxels take
   // 0.72 of the time of 128), or the wider tile's window would not fit
   const bool one = g->n[2] <= 64 || g->tile_rows[1] > kTileMaxRows;
   auto run = [&](int slices) { return one ? run_tiles<1>(g, a, slices, s) : run_tiles<2>(g, a, slices, s); };
-  if (!part) {
+  const bool both = axes == 3;
+  a.m0 = axes == 2 ? 1 : 0;
+  if (!part || (!both && splits == 1)) {  // into the volume, one launch per driving axis
+    a.vol = vol;
     int st = run(1);
     a.m0 = 1;
     a.accumulate = 1;
-    if (st == 0) st = run(1);
+    if (st == 0 && both) st = run(1);
     return st;
   }
-  const int st = run(2 * splits);
+  a.accumulate = 0;
+  a.splits = splits;
+  a.both = both ? 1 : 0;
+  const int slices = both ? 2 * splits : splits;
+  const int st = run(slices);
   if (st != 0) return st;
-  return launch_adjoint_sum(part, a.slice, 2 * splits, accumulate, vol, s);
+  return launch_adjoint_sum(part, a.slice, slices, accumulate, vol, s);
 }
 
 int launch_adjoint_sum(const float* part, size_t slice, int n_slices, bool accumulate, float* vol,

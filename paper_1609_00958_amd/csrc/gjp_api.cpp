@@ -340,9 +340,10 @@ static bool columns_share_inplane_setup(const gjp_geometry& g) {
 // false if the geometry is not one it handles: column geometries in which every
 // source lies in front of all tiles (tiles reach up to seven voxels past the
 // grid's upper ends), seen from every column.
-static bool tile_rows(const gjp_geometry& g, double rows[2]) {
+static bool tile_rows(gjp_geometry& g, double rows[2]) {
   rows[0] = rows[1] = 0.0;
   if (!g.separable) return false;
+  g.axes.assign((size_t)g.n_views, 0);
   const double kOver = 20.0;  // tile overhang plus margin (voxels)
   for (int v = 0; v < g.n_views; ++v) {
     const double* o = g.views_grid.data() + 12 * (size_t)v;
@@ -377,6 +378,7 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
       }
       for (int m = 0; m < 2; ++m) {
         if (!used[m]) continue;
+        g.axes[(size_t)v] |= (uint8_t)(1 << m);
         double d;
         if (o[m] < -3.0 && r_lo[m] > 0.0)
           d = -o[m];
@@ -390,6 +392,7 @@ static bool tile_rows(const gjp_geometry& g, double rows[2]) {
         b_min = std::min(b_min, b1 * d / r_abs[m]);
       }
     }
+    if (g.beam == GJP_PARALLEL) g.axes[(size_t)v] = fabs(o[1]) > fabs(o[0]) ? 2 : 1;
     // a tile's own extent, plus how far its rows shift over its planes and
     // columns (cone: the spread of the magnification at the far end of axis 2;
     // parallel: rays climb less than one voxel per plane): ordinarily far below these
@@ -638,7 +641,11 @@ extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geomet
   g->rows = rows_per_lane(*g, g->rows_pay);
   g->deal = deals_tiles_by_rule(*g, g->deal_tile);
   g->free_gather = gathers_freely(*g);
-  g->tiles = tile_rows(*g, rows) && rows[0] <= gjp::kTileMaxRows && g->n_u <= gjp::kTileMaxColumns;
+  try {
+    g->tiles = tile_rows(*g, rows) && rows[0] <= gjp::kTileMaxRows && g->n_u <= gjp::kTileMaxColumns;
+  } catch (...) {
+    return fail(GJP_ENOMEM, "gjp_create_geometry: host allocation failed");
+  }
   for (int k = 0; k < 2; ++k) g->tile_rows[k] = g->tiles ? (int)std::min(rows[k], 1.0e9) : 0;
   *out = g.release();
   return GJP_OK;
@@ -1301,15 +1308,15 @@ static gjp_status back_project_tiles(const gjp_geometry* g, const double* d_view
   const size_t vol = (size_t)g->n[0] * g->n[1] * g->n[2] * sizeof(float);
   void* rays = nullptr;
   size_t ray_bytes = 0, part = 0;
-  for (bool parts = true;;) {  // fewer views at a time where the device has no room for their rays
-    part = parts ? 2 * (size_t)gjp::adjoint_tile_splits(g->n, (int)chunk) * vol : 0;
+  // fewer views at a time where the device has no room for their rays (and their partial
+  // volumes, which one or two views have none of)
+  for (;;) {
+    part = 2 * (size_t)gjp::adjoint_tile_splits(g->n, (int)chunk) * vol;
     ray_bytes = ((size_t)chunk * per_view + 255) & ~(size_t)255;
     const hipError_t e = scratch_alloc(&rays, ray_bytes + part, s);
     if (e == hipSuccess) break;
-    if (e != hipErrorOutOfMemory || (chunk == 1 && part == 0))
-      return hip_fail(e, "back_project: scaled rays");
+    if (e != hipErrorOutOfMemory || chunk == 1) return hip_fail(e, "back_project: scaled rays");
     (void)hipGetLastError();
-    if (chunk == 1) parts = false;  // then without partial volumes
     chunk = (chunk + 3) / 4;
   }
   const float4* parts = part ? reinterpret_cast<const float4*>(static_cast<char*>(rays) + ray_bytes)

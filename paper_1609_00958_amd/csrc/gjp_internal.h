@@ -40,8 +40,10 @@ struct gjp_geometry {
   bool free_gather = false;  // general geometry that adj_free_kernel takes
   // The adjoint runs as launch_adjoint_tiles, whose tiles of 64 and 128 voxels
   // along axis 2 need at most tile_rows[0] and tile_rows[1] detector rows.
+  // axes: bit m set in a view's entry if axis m drives one of its columns.
   bool tiles = false;
   int tile_rows[2] = {0, 0};
+  std::vector<uint8_t> axes;
 
   // device copies, per device (created on first use)
   struct Dev {
@@ -75,9 +77,11 @@ constexpr int kColumnPad = 8;
 // at least six views each (a split costs a partial volume's write and read):
 // 64^3 / 64 views 193 us as two launches, 103, 62, 52, 48 and 57 us with 1, 2,
 // 4, 8 and 16 splits; 128^3 / 12 views 76 us, then 58, 55 and 65 us with 1, 2
-// and 4. Partial volumes of more than 128 MB: 0, two launches into the volume
-// itself (256^3 / 360 views 5.7 ms, 5.5 with one split; 512^3 80 ms).
+// and 4. Partial volumes of more than 128 MB, or one or two views: 0, a launch per
+// driving axis into the volume itself (256^3 / 360 views 5.7 ms, 5.5 with one split;
+// 512^3 80 ms; 256^3 / 2 views 83 us, 96 with one split; / 1 view at 45 degrees 74, 89).
 inline int adjoint_tile_splits(const int* n, int n_views) {
+  if (n_views <= 2) return 0;
   const size_t vol = (size_t)n[0] * n[1] * n[2] * sizeof(float);
   const size_t tiles = (size_t)((n[0] + kTileEdge - 1) / kTileEdge) *
                        ((n[1] + kTileEdge - 1) / kTileEdge) * ((n[2] + 127) / 128);
@@ -180,13 +184,14 @@ int launch_adjoint_value_table(const gjp_geometry* g, const double* views, const
                                hipStream_t s);
 // Tile adjoint of column geometries (gjp_adjoint_tiles.hip): n_views views
 // (views, proj: the first one's entries) of rays scaled by their step lengths
-// (launch_adjoint_scale); adds to vol or overwrites it. part: scratch for 2 x
-// splits partial volumes, splits = adjoint_tile_splits; null for 0 splits.
+// (launch_adjoint_scale), driven by axis 0 (axes: bit 0), 1 (bit 1) or both; adds to vol
+// or overwrites it. part: scratch for 2 x splits partial volumes, splits =
+// adjoint_tile_splits; null for 0 splits.
 int launch_adjoint_scale(const gjp_geometry* g, const double* views, const float* sino, int n_views,
                          float* out, hipStream_t s);
 int launch_adjoint_tiles(const gjp_geometry* g, const double* views, const float* proj,
-                         const float* rays, int n_views, bool accumulate, float* vol, float* part,
-                         int splits, hipStream_t s);
+                         const float* rays, int n_views, int axes, bool accumulate, float* vol,
+                         float* part, int splits, hipStream_t s);
 // Sum of partial volumes (slice floats each), added to vol if accumulate.
 int launch_adjoint_sum(const float* part, size_t slice, int n_slices, bool accumulate, float* vol,
                        hipStream_t s);

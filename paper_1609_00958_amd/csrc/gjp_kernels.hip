@@ -2260,9 +2260,11 @@ int launch_adjoint_gather(const gjp_geometry* g, const float* proj, const float4
     int st = geometry_device(g, &views, &proj);
     const int splits = cols ? adjoint_tile_splits(g->n, n_chunk) : 0;
     float* part = splits ? reinterpret_cast<float*>(const_cast<float4*>(cols)) : nullptr;
+    int axes = 0;
+    for (int v = view0; v < view0 + n_chunk; ++v) axes |= g->axes[(size_t)v];
     if (st == 0)
       st = launch_adjoint_tiles(g, views + 12 * (size_t)view0, proj + 12 * (size_t)view0, vals,
-                                n_chunk, accumulate, vol, part, splits, s);
+                                n_chunk, axes, accumulate, vol, part, splits, s);
     timing_end("adjoint_gather", t, s);
     return st;
   }

@@ -98,3 +98,25 @@ def test_columns_that_climb(gjp, oracle_mod, climb):
     v[:, 5] -= climb * 0.5 * (n_u - 1)
     G = gjp.Geometry(shape, v, n_u, n_v, beam="parallel")
     _check(gjp, oracle_mod, G, 15, f"columns climbing {climb}")
+
+
+@pytest.mark.parametrize("n_views", [1, 3, 14])
+@pytest.mark.parametrize("beam", ["cone", "parallel"])
+@pytest.mark.parametrize("centre", [0, 45, 90, 170])
+def test_views_of_one_axis(gjp, oracle_mod, beam, centre, n_views):
+    """Views within a few degrees: columns of one driving axis (one pass over the volume, or
+    partial volumes of that axis only) or, about 45 degrees, of both."""
+    shape, n_u, n_v = (33, 30, 70), 50, 80
+    v = (gjp.views_circular_cone(360, 200.0, 300.0, 1.2, 1.5, n_u, n_v) if beam == "cone"
+         else gjp.views_parallel(360, 1.0, 0.9, n_u, n_v))
+    v = v[[(centre + k - n_views // 2) % 360 for k in range(n_views)]]
+    G = gjp.Geometry(shape, v, n_u, n_v, beam=beam)
+    _check(gjp, oracle_mod, G, 18, f"{beam}, {n_views} views about {centre} degrees")
+
+
+@pytest.mark.parametrize("views", [[0], [45], [10, 100]])
+def test_few_views_of_a_large_volume(gjp, oracle_mod, views):
+    """One pass, two of which the second adds to half of the tiles, two."""
+    shape, n_u, n_v = (208, 204, 200), 90, 70
+    v = gjp.views_circular_cone(360, 800.0, 1200.0, 5.0, 4.5, n_u, n_v)[views]
+    _check(gjp, oracle_mod, gjp.Geometry(shape, v, n_u, n_v), 19, f"large volume, views {views}")
