@@ -477,14 +477,15 @@ static bool gathers_freely(const gjp_geometry& g) {
 // Launch of a general geometry's forward (FwdArgs::spread): tile shape and whether its
 // tiles are dealt to the XCDs. Dealt tiles end evenly and take four planes' loads
 // together, but neighbouring tiles read the volume through different L2s. That costs
-// where rays lie more than a voxel or two apart and there are tiles enough to fill the
-// chip without it (120 x 130 x 110, 48 views of 60^2 152 us dealt, 89 in groups of views;
-// 140^2 254 and 297, 400^2 421 and 926; 30^2, fewer tiles than compute units, 53 and
-// 84; 240^3, 200^2 1.38 and 1.80 ms), and in views whose columns lie along axis 2, where
-// groups take the row-uniform loop (128^3, wide cone, 324 and 242 us). Few columns:
-// wavefronts along v (60^3, 400 views of 1 x 400 82 us with 16 x 16 tiles, 36 with 4 x 64;
-// in groups 42). Few rows: groups' tiles are 64 rows long (48 views of 400 x 4 73 and
-// 125 us; fewer tiles than half the compute units, one row 46 and 34).
+// where a view has few tiles, each of them as wide as a good part of the volume (90 x 100 x
+// 80, 48 views of 81 x 72 193 us dealt, 77 in groups of views; 120 x 130 x 110, 60^2 152 and
+// 89), unless rays lie close (60 x 70 x 50, 100 views of 90^2 59 and 88 us) or the tiles are
+// no more than one to an XCD or to a compute unit (48 views of 30^2 53 and 84); from some
+// eighty tiles on they gain (140^2 254 and 297, 400^2 421 and 926). Views whose columns
+// lie along axis 2 take the row-uniform loop in groups (128^3, wide cone, 324 and 242 us).
+// Few columns: wavefronts along v (60^3, 400 views of 1 x 400 82 us with 16 x 16 tiles, 36
+// with 4 x 64; in groups 42). Few rows: groups' tiles are 64 rows long (48 views of 400 x 4
+// 73 and 125 us; one row and fewer tiles than half the compute units, 46 and 34).
 static bool deals_tiles_by_rule(const gjp_geometry& g, int& tile) {
   tile = 4;
   if (g.separable) return false;
@@ -510,12 +511,17 @@ static bool deals_tiles_by_rule(const gjp_geometry& g, int& tile) {
   pv /= g.n_views;
   // lanes along v where there are few columns
   tile = g.n_u <= 4 || (g.n_u <= 12 && pv >= 8.0 * pu) ? 6 : g.n_u <= 8 ? 5 : 4;
-  const double tiles = (double)g.n_views * ceil((double)g.n_u / gjp::tile_u_columns(tile)) *
-                       ceil((double)g.n_v / gjp::tile_v_pixels(tile));
+  const double tu = ceil((double)g.n_u / gjp::tile_u_columns(tile));
+  const double tv = ceil((double)g.n_v / gjp::tile_v_pixels(tile));
+  const double view = tu * tv, tiles = view * g.n_views;
   if (2 * columns > g.n_views || tiles > 1.0e6) return false;
   if (g.n_v < 16) return g.n_v > 2 || tiles > 128.0;
   if (g.n_u <= 4) return g.n_u == 1 || tiles <= 1024.0;
-  return tiles <= (g.n_u < 16 ? 256.0 : 512.0) || tiles * std::max(pu, pv) >= 950.0;
+  if (g.n_u < 16) return tiles <= 256.0;
+  const double spacing = 1.0 / sqrt(pu * pv);  // voxels between rays
+  return view >= 80.0 || std::max(tu, tv) >= 16.0 ||
+         (view >= 36.0 && spacing <= (tiles < 5000.0 ? 1.85 : 2.3)) || view <= 8.0 ||
+         (tiles <= 256.0 && view <= 16.0);
 }
 
 // Rays per lane of the row forward (gjp_forward_rows.hip), or 0 where it cannot take the

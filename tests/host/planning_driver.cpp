@@ -481,9 +481,13 @@ static int dispatch_main() {
   gjp_destroy_geometry(g);
   CHECK(gjp_views_circular_cone(30, 256, 512, 2, 2, 64, 64, v.data()) == GJP_OK);
   for (int k = 0; k < 30; ++k) v[12 * k + 9] = 0.3;
-  g = make(n, GJP_CONE, 30, 64, 64, v.data());
-  CHECK(g && g->deal && g->deal_tile == 4);
-  gjp_destroy_geometry(g);
+  const int det[][4] = {{64, 64, 0, 4}, {180, 180, 1, 4}, {1, 200, 1, 6}, {7, 100, 1, 5},
+                        {200, 3, 1, 4}, {30, 30, 1, 4}, {40, 300, 1, 4}};
+  for (const auto& d : det) {
+    g = make(n, GJP_CONE, 30, d[0], d[1], v.data());
+    CHECK(g && g->deal == (d[2] != 0) && g->deal_tile == d[3]);
+    gjp_destroy_geometry(g);
+  }
   for (int k = 0; k < 30; ++k)  // and sources inside the grid
     for (int j = 0; j < 3; ++j) v[12 * k + j] *= 0.05;
   g = make(n, GJP_CONE, 30, 64, 64, v.data());
