@@ -194,12 +194,16 @@ __global__ __launch_bounds__(256) void pad_kernel(const E* __restrict__ src, E* 
 // Forward projection of one ray (Algorithm 1).
 // ---------------------------------------------------------------------------
 
-// Planes whose loads a lane of the per-lane loops issues together. The tile kernels take
-// two (axis 2: one), which keeps their registers, and so their occupancy, for the
-// row-uniform loop; the kernel of dealt tiles (GRP 0) takes four.
-template <int GRP>
+// Planes whose loads a lane of the per-lane loops issues together. The tile kernels of one
+// and two rays per lane take two (axis 2: one), which keeps their registers, and so their
+// occupancy, for the row-uniform loop (512 x 512 x 2, 360 views, 16-wide tiles 977 us, with
+// four 1117); the kernel of dealt tiles (GRP 0) and that of three rays per lane take four
+// (BF16 174 x 187 x 161, 36 views of 266 x 141, whose last rays do not fill their tile,
+// 374 -> 320 us; two rays per lane and 512^3 with four 7.33 -> 7.50 ms).
+template <int GRP, int RPL>
 struct Together {
-  static constexpr int buf = GRP == 0 ? 4 : 2, axis2 = GRP == 0 ? 4 : 1;
+  static constexpr bool four = GRP == 0 || RPL == 3;
+  static constexpr int buf = four ? 4 : 2, axis2 = four ? 4 : 1;
   static constexpr int uniform = GRP == 0 ? 4 : GRP;
 };
 
@@ -410,7 +414,7 @@ __device__ __forceinline__ float fwd_loop_rowuniform(const FwdArgs& a, const Ray
 // wavefront call this together; a lane without samples (R.i0 == R.i1, e.g. a
 // pixel outside the detector) takes part in the wavefront-wide steps and its
 // sum is meaningless.
-template <typename T, int WF, bool IDX64, int GRP>
+template <typename T, int WF, bool IDX64, int GRP, int RPL>
 __device__ __forceinline__ float fwd_sum(const FwdArgs& a, const RaySetup& R) {
   float acc = 0.0f;
   // row-uniform wavefront: every lane with samples shares m (0 or 1), ca and
@@ -432,12 +436,12 @@ __device__ __forceinline__ float fwd_sum(const FwdArgs& a, const RaySetup& R) {
     const int hi = __builtin_amdgcn_readfirstlane(wave_max(has ? R.i1 : -1));
     const int mid_lo = __builtin_amdgcn_readfirstlane(wave_max(has ? R.i0 : -1));
     const int mid_hi = __builtin_amdgcn_readfirstlane(wave_min(has ? R.i1 : 0x7fffffff));
-    acc = fwd_loop_rowuniform<T, WF, Together<GRP>::uniform>(a, R, lm, lca, lga, lo, hi, mid_lo,
+    acc = fwd_loop_rowuniform<T, WF, Together<GRP, RPL>::uniform>(a, R, lm, lca, lga, lo, hi, mid_lo,
                                                              mid_hi);
     if (!has) acc = 0.0f;
   } else if (R.m != 2) {
     if constexpr (!IDX64)
-      acc = fwd_loop_buf<T, WF, Together<GRP>::buf>(a, R);
+      acc = fwd_loop_buf<T, WF, Together<GRP, RPL>::buf>(a, R);
     else
       acc = fwd_loop_ptr<T, WF>(a, R);
   } else {
@@ -446,8 +450,8 @@ __device__ __forceinline__ float fwd_sum(const FwdArgs& a, const RaySetup& R) {
     const T* base = static_cast<const T*>(a.vol_a);
     const long long S0 = a.S0, S1 = a.S1;
     const float hia = a.G.hi[0], hib = a.G.hi[1];
-    if constexpr (Together<GRP>::axis2 > 1) {
-      constexpr int NP = Together<GRP>::axis2;
+    if constexpr (Together<GRP, RPL>::axis2 > 1) {
+      constexpr int NP = Together<GRP, RPL>::axis2;
       // (after the ray's last plane: its last again, not added)
       for (int i = R.i0; i < R.i1; i += NP) {
         Quad q[NP];
@@ -487,12 +491,12 @@ __device__ __forceinline__ float fwd_sum(const FwdArgs& a, const RaySetup& R) {
   return acc;
 }
 
-template <typename T, int WF, bool IDX64, int GRP>
+template <typename T, int WF, bool IDX64, int GRP, int RPL = 1>
 __device__ __forceinline__ void fwd_ray(const FwdArgs& a, int view, int iu, int iv, bool valid) {
   RaySetup R;
   ray_setup(a.views + 12 * (size_t)view, a.G, iu, iv, R);
   if (!valid) R.i1 = R.i0;
-  const float acc = fwd_sum<T, WF, IDX64, GRP>(a, R);
+  const float acc = fwd_sum<T, WF, IDX64, GRP, RPL>(a, R);
   if (valid) a.sino[((size_t)view * a.n_u + iu) * a.n_v + iv] = acc * R.scale;
 }
 
@@ -1038,9 +1042,9 @@ __device__ __forceinline__ void fwd_ray_triple(const FwdArgs& a, int view, int i
   } else {
     // one ray set after another; the setups are recomputed so that they do
     // not stay live through the other rays' loops
-    fwd_ray<T, WF, IDX64, GRP>(a, view, iu, iv, valid1);
-    fwd_ray<T, WF, IDX64, GRP>(a, view, iu, iv + 1, valid2);
-    fwd_ray<T, WF, IDX64, GRP>(a, view, iu, iv + 2, valid3);
+    fwd_ray<T, WF, IDX64, GRP, 3>(a, view, iu, iv, valid1);
+    fwd_ray<T, WF, IDX64, GRP, 3>(a, view, iu, iv + 1, valid2);
+    fwd_ray<T, WF, IDX64, GRP, 3>(a, view, iu, iv + 2, valid3);
   }
 }
 
