@@ -526,23 +526,17 @@ static bool deals_tiles_by_rule(const gjp_geometry& g, int& tile) {
 
 // Rays per lane of the row forward (gjp_forward_rows.hip), or 0 where it cannot take the
 // geometry: not a column geometry, or rays so far apart that 128 of them span more than
-// the window. pay: it is the default; else there are too few rays in a column to share
-// its rows, and the padded copies are sampled. The costs are times per column and plane
-// as measured at 256^3, 360 views of 384 columns (1 = 1 ms in all): a wavefront of 64 r
-// rays 1.81, 2.05, 2.25 and 3.26 for r = 2, 3, 4 and 6 (with voxels of a second load:
-// +0.5; 16-bit volumes a tenth more), a wavefront of the copies' kernel 0.92 per 64 rays;
-// their two copies take 14 us and 6.5 ps per voxel. 64^3, 64 x 64 rays: 22 against 31 us
-// for 64 views, 93 against 64 us for 360. 16-bit copies that fit the L2s: 0.83 (128^3, 200
-// views of 192 x 128 307 us against 286; 256^3, 100 views of 384 x 128 657 against 726).
-static int rows_per_lane(const gjp_geometry& g, bool pay[2]) {
-  pay[0] = pay[1] = false;
+// the window. Its cost is the time per column and plane as measured at 256^3, 360 views of
+// 384 columns (1 = 1 ms in all): a wavefront of 64 r rays 1.81, 2.05, 2.25 and 3.26 for r =
+// 2, 3, 4 and 6 (with voxels of a second load: +0.5).
+static int rows_per_lane(const gjp_geometry& g, double& best_cost) {
   if (!g.separable) return 0;
   const double s0 = (double)g.n[1] * g.n[2] * 4.0, s1 = (double)g.n[2] * 4.0;
   if (66.0 * (s0 + s1) >= 2147483648.0) return 0;  // 31-bit offsets within 64 planes
   double b, climb;
   column_spacing(g, b, climb);
   int best = 0;
-  double best_cost = 1.0e300;
+  best_cost = 1.0e300;
   for (int r : {2, 3, 4, 6}) {
     // (9: RowWindow's rounding at both ends and to groups of four)
     const double window = (64.0 * r - 1.0) * b + (gjp::kRowPlanes - 1.0) * climb + 9.0;
@@ -554,13 +548,6 @@ static int rows_per_lane(const gjp_geometry& g, bool pay[2]) {
       best = r;
     }
   }
-  const double planes = (double)std::max(g.n[0], g.n[1]) * g.n_u * g.n_views;
-  const double voxels = (double)g.n[0] * g.n[1] * g.n[2];
-  if (best == 0) return 0;
-  const double waves = ceil(g.n_v / 64.0), l2 = 32.0 * 1024 * 1024;
-  pay[0] = 28.0e-12 * planes * (best_cost - 0.92 * waves) <= 14.0e-6 + 6.5e-12 * voxels;
-  pay[1] = 28.0e-12 * planes * (1.1 * best_cost - (4.0 * voxels <= l2 ? 0.83 : 1.17) * waves) <=
-           14.0e-6 + 4.0e-12 * voxels;
   return best;
 }
 
@@ -644,7 +631,7 @@ extern "C" gjp_status gjp_create_geometry(const gjp_geometry_desc* d, gjp_geomet
   }
   g->separable = columns_share_inplane_setup(*g);
   double rows[2];
-  g->rows = rows_per_lane(*g, g->rows_pay);
+  g->rows = rows_per_lane(*g, g->rows_cost);
   g->deal = deals_tiles_by_rule(*g, g->deal_tile);
   g->free_gather = gathers_freely(*g);
   try {
@@ -983,11 +970,29 @@ long long padded_elems(const int* n) {
   return (long long)(n[0] + 2) * (long long)(n[1] + 2) * gjp::padded_pitch(n[2]);
 }
 
+// Whether the row forward is the default, or there are too few rays in a column to share
+// its rows. In rows_per_lane's costs a wavefront of the copies' kernel takes 0.92 per 64
+// rays of the set tile; its two copies take 14 us and 6.5 ps per voxel: 64^3, 64 x 64
+// rays, 64 views 31 us, rows 22, 360 views 64 and 93. 16-bit rows cost a tenth more, 16-bit
+// copies less: 4 ps per voxel, and 0.83 where they fit the L2s (128^3, 200 views of 192 x
+// 128 286 us, rows 307; 256^3, 100 views of 384 x 128 726 and 657).
+bool rows_pay(const gjp_geometry* g, int dtype, int tile_v_log2) {
+  const int tile = std::max(64, gjp::tile_v_pixels(tile_v_log2));
+  const double waves = ceil((double)g->n_v / tile) * (tile / 64);
+  const double planes = (double)std::max(g->n[0], g->n[1]) * g->n_u * g->n_views;
+  const double voxels = (double)g->n[0] * g->n[1] * g->n[2];
+  if (dtype == GJP_F32)
+    return 28.0e-12 * planes * (g->rows_cost - 0.92 * waves) <= 14.0e-6 + 6.5e-12 * voxels;
+  const double wave = 8.0 * voxels <= 32.0 * 1024 * 1024 ? 0.83 : 1.17;  // both copies
+  return 28.0e-12 * planes * (1.1 * g->rows_cost - wave * waves) <= 14.0e-6 + 4.0e-12 * voxels;
+}
+
 // Rays per lane of the row forward, or 0 where the padded copies are sampled.
 // 16-bit rows that do not all start on 4 bytes would have to be read element by
 // element: 81 us instead of 42 for FP16 97 x 83 x 121 and 45 views of 129 x 101.
 int rows_of(const gjp_geometry* g, const void* d_vol, int dtype, const FwdTile& tile) {
-  if (tile.path == FwdTile::BY_RULE ? !g->rows_pay[dtype != GJP_F32] : tile.path == FwdTile::TILES) return 0;
+  if (!g->rows || tile.path == FwdTile::TILES) return 0;
+  if (tile.path == FwdTile::BY_RULE && !rows_pay(g, dtype, tile.tile_v_log2)) return 0;
   return dtype == GJP_F32 || (g->n[2] % 2 == 0 && (uintptr_t)d_vol % 4 == 0) ? g->rows : 0;
 }
 
@@ -1176,22 +1181,29 @@ extern "C" gjp_status gjp_autotune_forward(const gjp_geometry* g, const void* d_
   GJP_HIP(hipEventCreate(&e1), "autotune event");
   FwdTile best;
   float best_ms = 3.0e38f;
-  // time one candidate: a warm-up call, then three timed calls
+  // time one candidate: a warm-up call, then three timed calls, or thirty where those take
+  // under half a millisecond (clocks and other streams' work weigh more than a kernel)
   auto trial = [&](const FwdTile& t) -> gjp_status {
     gjp_status r = forward_with_tile(g, d_vol, vol_dtype, d_sino, s, t);  // warm-up
-    if (r != GJP_OK) return r;
-    hipError_t he = hipEventRecord(e0, s);
-    const int reps = 3;
-    for (int i = 0; i < reps && r == GJP_OK && he == hipSuccess; ++i)
-      r = forward_with_tile(g, d_vol, vol_dtype, d_sino, s, t);
-    if (he == hipSuccess) he = hipEventRecord(e1, s);
-    if (he == hipSuccess) he = hipEventSynchronize(e1);
-    if (r != GJP_OK) return r;
-    if (he != hipSuccess) return hip_fail(he, "autotune timing");
     float ms = 0.0f;
-    he = hipEventElapsedTime(&ms, e0, e1);
-    if (he != hipSuccess) return hip_fail(he, "autotune elapsed");
-    if (ms < best_ms) {
+    for (int reps : {3, 30}) {
+      if (r != GJP_OK) return r;
+      hipError_t he = hipEventRecord(e0, s);
+      for (int i = 0; i < reps && r == GJP_OK && he == hipSuccess; ++i)
+        r = forward_with_tile(g, d_vol, vol_dtype, d_sino, s, t);
+      if (he == hipSuccess) he = hipEventRecord(e1, s);
+      if (he == hipSuccess) he = hipEventSynchronize(e1);
+      if (r != GJP_OK) return r;
+      if (he != hipSuccess) return hip_fail(he, "autotune timing");
+      he = hipEventElapsedTime(&ms, e0, e1);
+      if (he != hipSuccess) return hip_fail(he, "autotune elapsed");
+      const bool enough = ms > 0.5f;
+      ms /= (float)reps;
+      if (enough) break;
+    }
+    // (a burst of short calls hides the allocation of the copies, 8 us of a call alone)
+    const bool copies = t.path == FwdTile::TILES && best.path == FwdTile::OWN && best_ms < 0.1f;
+    if (ms < (copies ? 0.85f : 1.0f) * best_ms) {
       best_ms = ms;
       best = t;
     }

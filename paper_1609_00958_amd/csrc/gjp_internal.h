@@ -29,10 +29,9 @@ struct gjp_geometry {
   // adjoint uses the column-form gather.
   bool separable = false;
   // Rays per lane of the row forward (gjp_forward_rows.hip); 0: it cannot take the
-  // geometry. rows_pay: it is the default (else the padded copies are), for FP32 and
-  // 16-bit volumes.
+  // geometry. rows_cost: its time per column and plane (rows_per_lane).
   int rows = 0;
-  bool rows_pay[2] = {false, false};
+  double rows_cost = 0.0;
   // General geometries: tile_v_log2 of the dealt tiles (FwdArgs::spread); deal: they are
   // the default (else groups of views with the set tile are).
   int deal_tile = 4;

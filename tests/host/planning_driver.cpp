@@ -23,7 +23,11 @@ int launch_sart_residual(long long, const float*, const float*, const float*, fl
 int launch_sart_update(long long, float*, const float*, const float*, float, int, hipStream_t) {
   return 0;
 }
-int launch_forward(const FwdArgs&, int, int, bool, int, hipStream_t) { return 0; }
+static int g_forward_rows = -1;
+int launch_forward(const FwdArgs& a, int, int, bool, int, hipStream_t) {
+  g_forward_rows = a.rows;
+  return 0;
+}
 int launch_forward_naive(const GridGeom&, const double*, const void*, int, int, int, int, int,
                          float*, hipStream_t) { return 0; }
 int launch_adjoint_table(const gjp_geometry*, const double*, const float*, int, int, float4*,
@@ -441,6 +445,16 @@ static int columns_main() {
   return 0;
 }
 
+// Whether a forward runs without padded copies (set tile shape; 0: the default).
+static bool rows_taken(const gjp_geometry* g, int dtype, int tile) {
+  CHECK(gjp_set_forward_tile(g, dtype, tile, 8, 4) == GJP_OK);
+  g_largest = 0;
+  gjp::g_forward_rows = -1;
+  CHECK(gjp_forward_project(g, (const void*)16, dtype, (float*)16, nullptr) == GJP_OK);
+  CHECK(gjp_set_forward_tile(g, dtype, 0, 8, 4) == GJP_OK);
+  return gjp::g_forward_rows > 0;
+}
+
 // The kernels that geometries of each kind are sent to.
 static int dispatch_main() {
   const int n[3] = {64, 60, 70};
@@ -449,7 +463,7 @@ static int dispatch_main() {
   CHECK(gjp_views_circular_cone(30, 256, 512, 2, 2, 64, 64, v.data()) == GJP_OK);
   g = make(n, GJP_CONE, 30, 64, 64, v.data());  // ordinary circular scan
   CHECK(g && g->separable && g->rows > 0 && g->tiles && !g->free_gather);
-  CHECK(g->rows_pay[0] && g->rows_pay[1]);
+  CHECK(rows_taken(g, GJP_F32, 0) && rows_taken(g, GJP_BF16, 0));
   gjp_destroy_geometry(g);
   {  // columns of 128 rays: rows for FP32, small 16-bit copies for 16 bits; 64: copies
     const int m[3] = {128, 128, 128};
@@ -458,7 +472,10 @@ static int dispatch_main() {
       CHECK(gjp_views_circular_cone(200, 512, 768, 1.0, 1.55 * 128 / n_v, 192, n_v, w.data()) ==
             GJP_OK);
       g = make(m, GJP_CONE, 200, 192, n_v, w.data());
-      CHECK(g && g->rows > 0 && g->rows_pay[0] == (n_v > 64) && g->rows_pay[1] == (n_v > 128));
+      CHECK(g && g->rows > 0 && rows_taken(g, GJP_F32, 0) == (n_v > 64));
+      CHECK(rows_taken(g, GJP_F16, 0) == (n_v > 128));
+      // a set tile of 192 rays, of which the copies' kernel would leave most idle
+      CHECK(n_v == 64 || (rows_taken(g, GJP_F32, 192) && rows_taken(g, GJP_BF16, 192)));
       gjp_destroy_geometry(g);
     }
   }
