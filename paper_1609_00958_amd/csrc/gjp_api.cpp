@@ -514,7 +514,8 @@ static bool deals_tiles_by_rule(const gjp_geometry& g, int& tile) {
   const double tu = ceil((double)g.n_u / gjp::tile_u_columns(tile));
   const double tv = ceil((double)g.n_v / gjp::tile_v_pixels(tile));
   const double view = tu * tv, tiles = view * g.n_views;
-  if (2 * columns > g.n_views || tiles > 1.0e6) return false;
+  // (dealt tiles are rounded up to whole rounds of the XCDs; 2^32 threads a launch)
+  if (2 * columns > g.n_views || (tu + 7.0) * tv * g.n_views >= 16.0e6) return false;
   if (g.n_v < 16) return g.n_v > 2 || tiles > 128.0;
   if (g.n_u <= 4) return g.n_u == 1 || tiles <= 1024.0;
   if (g.n_u < 16) return tiles <= 256.0;

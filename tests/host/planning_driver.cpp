@@ -498,6 +498,17 @@ static int dispatch_main() {
   gjp_destroy_geometry(g);
   CHECK(gjp_views_circular_cone(30, 256, 512, 2, 2, 64, 64, v.data()) == GJP_OK);
   for (int k = 0; k < 30; ++k) v[12 * k + 9] = 0.3;
+  {  // many views of many tiles, up to what one launch takes
+    std::vector<double> w(12 * 1500);
+    CHECK(gjp_views_circular_cone(1500, 256, 512, 0.2, 0.2, 1500, 1500, w.data()) == GJP_OK);
+    for (int k = 0; k < 1500; ++k) w[12 * k + 9] = 0.03;
+    g = make(n, GJP_CONE, 1500, 1500, 1500, w.data());
+    CHECK(g && !g->separable && g->deal);
+    gjp_destroy_geometry(g);
+    g = make(n, GJP_CONE, 1500, 1800, 1800, w.data());
+    CHECK(g && !g->separable && !g->deal);
+    gjp_destroy_geometry(g);
+  }
   const int det[][4] = {{64, 64, 0, 4}, {180, 180, 1, 4}, {1, 200, 1, 6}, {7, 100, 1, 5},
                         {200, 3, 1, 4}, {30, 30, 1, 4}, {40, 300, 1, 4}};
   for (const auto& d : det) {
