@@ -16,8 +16,8 @@ forward, 20 gradient-descent steps of the differentiable projector, one
 batched launch of the 32-instance uneven workload, the paper's speed geometry
 (Table I: ms per projection), a 1024^3 BF16/FP16 forward, a 2048^3 FP32
 forward and SART iterations on the 256^3 workload. `roofline` refers to the FP32 forward kernel and its
-binding unit (the vector ALUs); the HBM fraction from the
-committed byte counters and the paper's access rate are reported beside it.
+vector ALUs; the HBM fraction from the committed byte counters and the paper's
+access rate are reported beside it.
 
 Prints one JSON line on stdout; progress goes to stderr.
 """
@@ -37,7 +37,9 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 # FP32 vector lanes: 256 CUs x 4 SIMDs x 32 lanes per clock x 2.4 GHz.
 VALU_PEAK = 256 * 4 * 32 * 2.4e9
-VALU_OPS_PER_SAMPLE = 7
+# A sample of the row forward: position, lower weight and two FMAs at that rate;
+# voxel (a conversion), LDS address (a shift and add) and fraction at half of it.
+VALU_LANE_CYCLES_PER_SAMPLE = 4 * 1 + 3 * 2
 # The paper's GJP_lin FP32 forward, volume in global memory (Table I, Sec.
 # IV-C geometry): ms per projection.
 PAPER_T1_MS = {"GTX 1080": 2.70, "GTX 970": 5.69}
@@ -490,20 +492,21 @@ def main():
     log(f"FP32 forward: {step_ms:.2f} ms per step (kernel {fwd_ms:.2f} ms, pad "
         f"{r['pad']['ms_per_launch']:.2f} ms); {value:.4g} ray-samples/s")
 
-    # roofline of the FP32 forward kernel on the vector ALUs: a sample of the row
-    # forward takes seven lane operations (position, voxel, LDS address, fraction,
-    # lower weight, two FMAs) besides what its wavefront does once per plane
+    # roofline of the FP32 forward kernel on the vector ALUs: the lane cycles of its
+    # samples alone, seven instructions each. What a wavefront does once per plane
+    # (the window, four voxels' in-plane sums per lane, the rows' LDS writes) is
+    # five more per sample at 256 rays per wavefront and not counted as achieved.
     tile_cfg = gjp.get_forward_tile(G, torch.float32)
     fwd_kernel = "forward_f32_rows"
-    achieved = VALU_OPS_PER_SAMPLE * S / (fwd_ms * 1e-3)
+    achieved = VALU_LANE_CYCLES_PER_SAMPLE * S / (fwd_ms * 1e-3)
     traffic = measured_traffic(cfg.name, fwd_kernel)
     roofline = {
         "kernel": fwd_kernel,
         "bound": "valu",
         "achieved": achieved,
         "peak": VALU_PEAK,
-        "unit": "lane operations/s",
-        "lane_operations_per_sample": VALU_OPS_PER_SAMPLE,
+        "unit": "lane cycles/s",
+        "lane_cycles_per_sample": VALU_LANE_CYCLES_PER_SAMPLE,
         "frac": achieved / VALU_PEAK,
         "traffic": (traffic[0] + traffic[1]) if traffic else None,
         "hbm_GBps": ((traffic[0] + traffic[1]) / (fwd_ms * 1e-3) / 1e9) if traffic else None,
