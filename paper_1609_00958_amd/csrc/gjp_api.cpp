@@ -1490,13 +1490,20 @@ std::map<std::string, std::shared_ptr<BatchPlan>> g_plans;
 uint64_t g_plan_clock = 0;  // guarded by g_plan_mu
 constexpr size_t kMaxPlans = 8;
 
+// The batched launch runs the tuned tile with one or three rays per lane; a tuned
+// two-rays-per-lane tile becomes the one-ray tile (same sums), and one of three too where
+// single calls deal one-ray tiles.
+int batched_tile(const gjp_geometry* g, const FwdTile& t) {
+  return t.tile_v_log2 == 7 || (t.tile_v_log2 == 8 && deals_tiles(g, t)) ? 6 : t.tile_v_log2;
+}
+
 std::string plan_key(int n, const gjp_geometry* const* g, const void* const* d_vols,
                      const int32_t* dtypes, int dvc) {
   std::string k = std::to_string(dvc);
   for (int i = 0; i < n; ++i) {
     k += "|" + std::to_string(g[i]->id) + ":" + std::to_string(dtypes[i]);
     const FwdTile t = tile_for(g[i], dtypes[i]);
-    k += ":" + std::to_string(t.tile_v_log2) + ":" +
+    k += ":" + std::to_string(batched_tile(g[i], t)) + ":" +
          std::to_string(rows_of(g[i], d_vols[i], dtypes[i], t));
   }
   return k;
@@ -1582,9 +1589,7 @@ gjp_status build_plan(int n, const gjp_geometry* const* g, const void* const* d_
     const FwdTile tile = tile_for(g[i], dtypes[i]);
     FwdTile t2 = tile;
     t2.remap = 0;
-    // the batched launch runs the tuned tile with one or three rays per lane;
-    // a tuned two-rays-per-lane tile becomes the one-ray tile (same sums)
-    if (t2.tile_v_log2 == 7) t2.tile_v_log2 = 6;
+    t2.tile_v_log2 = batched_tile(g[i], tile);
     fill_fwd_args(g[i], d_views, rows_of(g[i], d_vols[i], dtypes[i], tile), nullptr, t2, I.a);
     if (!I.a.rows) {
       I.padded = static_cast<char*>(P->padded_all) + pad_off[i];

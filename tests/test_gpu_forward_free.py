@@ -86,3 +86,27 @@ def test_autotuned_choice(oracle_mod, tmp_path, monkeypatch, kind, dtype):
     assert torch.equal(gjp.forward(d, G), y)
     for entry in path.read_text().splitlines():
         assert len(entry.split()) in (5, 6)
+
+
+@pytest.mark.parametrize("tile", [192, 64, 16])
+def test_batched_views_in_columns(oracle_mod, tile):
+    """General geometry with a few views whose columns lie along axis 2: single calls
+    take the rule's kernel whatever tile is set, batched ones give the same bits."""
+    import torch
+
+    import paper_1609_00958_amd as gjp
+    shape, n_u, n_v = (40, 36, 50), 64, 400
+    views = gjp.views_circular_cone(9, 160.0, 320.0, 1.0, 0.3, n_u, n_v).reshape(9, 12)
+    views[2:, 9] = 0.01  # seven of nine tilted
+    G = gjp.Geometry(shape, views, n_u, n_v)
+    og = oracle_mod.Geometry(G.shape, G.views, n_u, n_v, beam=oracle_mod.CONE)
+    x = np.random.default_rng(47).uniform(0, 1, size=shape).astype(np.float32)
+    note(f"general forward with columns, tile {tile}")
+    d = torch.from_numpy(x).to(cuda())
+    gjp.set_forward_tile(G, torch.float32, tile, 8, 4)
+    try:
+        y = gjp.forward(d, G)
+        assert_parity(y.cpu().numpy(), oracle_mod.forward(og, x), TOL32)
+        assert torch.equal(gjp.forward_batched([d], [G])[0], y)
+    finally:
+        gjp.reset_forward_tile(G, torch.float32)
