@@ -140,9 +140,10 @@ gjp_status gjp_forward_project_noalloc(const gjp_geometry *g, const void *d_vol,
 gjp_status gjp_forward_project_naive(const gjp_geometry *g, const void *d_vol,
                                      int32_t vol_dtype, float *d_sino, void *stream);
 
-/* Adjoint (exact transpose) x = A^T y of gjp_forward_project for the same
-   geometry: every sample's single-precision weights are recomputed exactly as
-   the forward computes them, up to rounding. When every view's dv is parallel
+/* Adjoint (transpose) x = A^T y of gjp_forward_project for the same geometry:
+   the same samples and weights, by other arithmetic than the forward's, so that
+   the two agree up to the rounding of single precision (relative L2 1e-5 of the
+   transpose in double precision). When every view's dv is parallel
    to axis 2, no ray is driven by axis 2 and the sources lie outside the grid
    (circular trajectories), tiles of voxels resample each detector column once
    per plane; column geometries with sources at or inside the grid gather per
@@ -151,11 +152,13 @@ gjp_status gjp_forward_project_naive(const gjp_geometry *g, const void *d_vol,
    samples are clipped, voxel tiles accumulate in LDS with waves owning disjoint
    planes. No atomics touch the volume; the sums are deterministic. d_sino:
    device, n_views*n_u*n_v floats. d_vol: device, n0*n1*n2 floats, overwritten.
-   Scratch for a chunk of views (the scaled rays, at most 2 GiB or one view, and
-   partial volumes of at most 256 MiB; per-ray tables of at most 512 MiB, with
-   such partial volumes for the cubes, on the other paths) is taken from the stream-ordered pool during the call (with the
-   same fallback as gjp_forward_project). Errors: GJP_EINVAL, GJP_ENOMEM,
-   GJP_EHIP. */
+   Scratch for a chunk of views is taken from the stream-ordered pool during the
+   call: the scaled rays, at most 2 GiB or one view, for the tiles; per-ray tables
+   of at most 512 MiB on the other paths; besides, partial volumes of at most 256
+   MiB for the tiles and cubes of small volumes. Allocation falls back as in
+   gjp_forward_project; where that fails too, the tiles take smaller chunks, down
+   to one view, and the cubes go without partial volumes. Errors: GJP_EINVAL,
+   GJP_ENOMEM, GJP_EHIP. */
 gjp_status gjp_back_project(const gjp_geometry *g, const float *d_sino, float *d_vol,
                             void *stream);
 
@@ -169,7 +172,8 @@ gjp_status gjp_back_project(const gjp_geometry *g, const float *d_sino, float *d
    gjp_set_forward_tile; a two-rays-per-lane choice runs as the one-ray tile,
    whose sums are the same); instances with three rays per lane, and those whose
    rows are read in place, form classes of their own, one persistent launch per
-   class. Each sinogram is bitwise
+   class; general geometries whose single calls deal one-ray tiles run one ray per
+   lane. Each sinogram is bitwise
    equal to the one gjp_forward_project produces for the same instance and
    tile shape. Arrays g, d_vols, dtypes, d_sinos are host
    arrays of length n >= 1; every d_sinos[i] holds n_views*n_u*n_v floats.
@@ -203,23 +207,27 @@ gjp_status gjp_views_parallel(int32_t n_views, double pitch_u, double pitch_v, i
 gjp_status gjp_count_samples(const gjp_geometry *g, uint64_t *out);
 
 /* Select the launch configuration of gjp_forward_project for this geometry
-   and dtype (ray-tile shape, views interleaved per tile, planes whose loads a
-   lane issues together) by timing candidates on `stream` with the caller's
-   buffers (d_sino is overwritten); the sums do not depend on the
-   configuration beyond rounding order (every one matches the oracle within
-   the stated tolerance). The choice is kept for this process, keyed by the
+   and dtype (kernels, ray-tile shape, views interleaved per tile, planes whose
+   loads a lane issues together) by timing candidates on `stream` with the caller's
+   buffers (d_sino is overwritten): the geometry's own kernel (rows read in place,
+   or the dealt tiles of general geometries), then the tiles sampling the padded
+   copies. The sums do not depend on the configuration beyond rounding order
+   (every one matches the oracle within the stated tolerance; rows read in place,
+   three pixels per lane and the other tiles differ in it). The choice is kept for
+   this process, keyed by the
    geometry's shape signature (grid, views, detector, beam, weight) and dtype,
    and used by later forward and batched calls. If the environment variable
    GJP_TUNE_CACHE names a file, the choice is also written there (one line
    per entry, tagged with the device's architecture name and compute-unit
-   count; replaced atomically by rename) and later processes on the same kind
+   count; a sixth field names the kernels where they are not those that the
+   geometry takes by rule; replaced atomically by rename) and later processes on the same kind
    of device read it instead of the default; an unreadable or unwritable
    file is ignored. *tile_v_out receives the chosen number of detector pixels
    along v per wavefront row (192 when three pixels per lane share their
    loads, any storage type; 128 when two do, 16-bit storage only; else 64, 32
-   or 16; 64 for geometries whose rows are read in place, which have no ray
-   tiles: their view group only is chosen; 64 too for general geometries, which
-   have one configuration). Synchronises `stream`.
+   or 16; 64 too where the rows are read in place, which has no ray tiles and of
+   which the view group only is chosen, and where the dealt tiles of a general
+   geometry are taken, which have one configuration). Synchronises `stream`.
    Errors: GJP_EINVAL, GJP_ENOMEM, GJP_EHIP. */
 gjp_status gjp_autotune_forward(const gjp_geometry *g, const void *d_vol, int32_t vol_dtype,
                                 float *d_sino, void *stream, int32_t *tile_v_out);
@@ -235,11 +243,13 @@ gjp_status gjp_autotune_forward(const gjp_geometry *g, const void *d_vol, int32_
    are the same); view_group =
    consecutive views that take their turn on each ray tile together (1 to
    64); load_group = planes whose volume loads a lane issues together (2 or
-   4). Geometries whose rows are read in place (gjp_forward_project) use
-   view_group only, general geometries (not column ones) have one configuration
-   of their own, except in batched calls. tile_v = 0 removes this process's choice (the on-disk cache or the
-   default applies again; the other arguments are ignored). Not written to
-   the on-disk cache. Host-only. Errors: GJP_EINVAL. */
+   4). Which kernels run stays by rule: column geometries with enough rays in a
+   column for tiles of that width read the rows in place and use view_group only;
+   general geometries whose tiles are dealt to the device's parts one by one
+   (by their number per view and the rays' distance) have one configuration of
+   their own; all others use the three arguments. tile_v = 0 removes this process's
+   choice (the on-disk cache or the default applies again; the other arguments are
+   ignored). Not written to the on-disk cache. Host-only. Errors: GJP_EINVAL. */
 gjp_status gjp_set_forward_tile(const gjp_geometry *g, int32_t vol_dtype, int32_t tile_v,
                                 int32_t view_group, int32_t load_group);
 

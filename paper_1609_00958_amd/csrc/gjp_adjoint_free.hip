@@ -16,11 +16,12 @@
 // Why: spreading each sample to its four voxels with LDS additions instead costs
 // four read-modify-writes per sample, for rays that mostly miss the tile's planes,
 // and stages every ray for the whole tile. What bounds the gather: the vector ALUs
-// (200 M wavefront instructions, about 85% of the time, for 120 x 136 x 112 voxels
-// and 48 views of 180 x 200; a ray takes 30 per cube, and five in six of the rays
-// walked have no weight in a given voxel); LDS is 34% busy. Spread -> gather, with
-// the ray table: that case 2.3 -> 0.36 ms; 40^3, 16 views of 44^2 378 -> 71 us; 64^3,
-// 32 views of 200^2 4.98 -> 0.18 ms; 160^3, 60 views of 250^2 3.10 -> 0.89 ms.
+// (200 M wavefront instructions, 56% of the time at two cycles each and about 85% at
+// the rates measured for them, for 120 x 136 x 112 voxels and 48 views of 180 x 200; a
+// ray takes 30 per cube, and five in six of the rays walked have no weight in a given
+// voxel); LDS is 34% busy. Spread -> gather, with the ray table: that case 2.3 -> 0.36
+// ms; 40^3, 16 views of 44^2 378 -> 71 us; 64^3, 32 views of 200^2 4.98 -> 0.18 ms;
+// 160^3, 60 views of 250^2 3.10 -> 0.89 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

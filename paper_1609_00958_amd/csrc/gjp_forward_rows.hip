@@ -15,17 +15,22 @@
 // irregular 16-byte load per sample (two per three samples where three rays of a
 // lane share them), which the address unit serves at four lanes per clock, and
 // two padded copies of the volume per call. Coalesced rows cost 32 bytes per
-// voxel row pair and 64 RPL rays. What bounds the kernel: the vector ALUs (75-90%
-// busy: a sample is seven instructions, three of them of half rate) and, behind
-// them, the L1's return path (62% of 64 bytes per clock; the rows come from L2,
-// since the wavefronts of neighbouring columns drift apart).
+// voxel row pair and 64 RPL rays. What bounds the kernel: the vector ALUs and the
+// vector memory path together. At 512^3, 720 views of 768^2 a sample takes 12.4
+// instructions, seven of its own (three of half rate) and the rest its share of the
+// plane's; at two cycles each they fill 56% of the ALUs' time, at the rates measured
+// for them one by one 75-90%. The data unit is busy 99% of the time (a quarter of
+// it waiting for L1: the rows come from L2, since the wavefronts of neighbouring
+// columns drift apart), the address unit 88%, LDS 62%. BF16, with half the bytes: 62,
+// 98, 83 and 59%, and 57 instead of 61 ms.
 // Measured steps, 256^3 / 360 views of 384^2: 4- and 8-byte loads 4.2 ms (the
 // return path gives 30 bytes per clock whatever their width below 16), 16-byte
 // loads 3.7 ms, the next planes' loads issued before the current ones are
 // sampled and all LDS reads of a plane before its sums 3.3 ms.
-// Copies' kernel -> this one: 256^3 as above 5.55 -> 3.32 ms, 512^3 / 720 views
-// of 768^2 74.8 -> 59.8 ms (its three-rays-per-lane tiles; 95 ms with one),
-// 1024^3 BF16 / 120 views of 1536^2 112 -> 91 ms, 64^3 / 64 views 34 -> 22 us.
+// Copies' kernel -> this one, uniform random volumes: 256^3 as above 5.7 -> 3.4 ms,
+// 512^3 / 720 views of 768^2 76.8 -> 60.7 ms (its three-rays-per-lane tiles; 95 ms
+// with one), 1024^3 BF16 / 120 views of 1536^2 115 -> 93 ms, 64^3 / 64 views 29 -> 22
+// us. A phantom that is half zeros takes 54 ms at 512^3 (likely the power limit).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

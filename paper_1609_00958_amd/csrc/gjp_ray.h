@@ -4,9 +4,11 @@
 // The ray setup (Eqs. 1-5, Algorithm 1 setup) runs in double precision and
 // yields the driving axis, the exact sample range and single-precision
 // coefficients of the two transverse coordinates; the sampling loop
-// (Eqs. 6-13) then runs in single precision. The forward and the adjoint
-// kernels evaluate a sample through the same `sample_axis` function, so the
-// adjoint reproduces the forward's weights bit for bit.
+// (Eqs. 6-13) then runs in single precision. Kernels that step single rays
+// (forward from the padded copies, ray tables, tile splat) evaluate a sample
+// through the same `sample_axis` function. Those of column geometries (row
+// forward, tile adjoint) and the cube gather form the same weights by other
+// arithmetic, equal up to rounding.
 //
 // This file must be compiled without floating-point contraction
 // (-ffp-contract=off): the driving axis and the sample range decide integer

@@ -198,6 +198,9 @@ DERIVED = (
     ("LDS instr / wave", lambda c: c["SQ_INSTS_LDS"] / c["SQ_WAVES"]),
     ("VALU issue (2 cycles / wave instr)",
      lambda c: 2.0 * c["SQ_INSTS_VALU"] / (1024.0 * c["GRBM_GUI_ACTIVE"] / 8.0)),
+    ("LDS busy (indexed)",
+     lambda c: 8.0 * c["SQ_LDS_IDX_ACTIVE"] / c["GRBM_GUI_ACTIVE"] / 256.0),
+    ("of it bank conflicts", lambda c: c["SQ_LDS_BANK_CONFLICT"] / c["SQ_LDS_IDX_ACTIVE"]),
     ("address unit busy (TA)", lambda c: 8.0 * c["TA_TA_BUSY_sum"] / c["GRBM_GUI_ACTIVE"] / 256.0),
     ("data unit busy (TD)", lambda c: 8.0 * c["TD_TD_BUSY_sum"] / c["GRBM_GUI_ACTIVE"] / 256.0),
     ("TA cycles / load instr", lambda c: c["TA_TA_BUSY_sum"] / c["SQ_INSTS_VMEM_RD"]),

@@ -250,7 +250,9 @@ def forward_batched(vols: Sequence, geoms: Sequence[Geometry], outs: Optional[Se
 
 
 def autotune(vol, geom: Geometry, out=None) -> int:
-    """Time the forward tile candidates for this geometry and dtype; returns tile_v."""
+    """Time the forward's kernels and tile candidates for this geometry and dtype
+    and keep the fastest; returns tile_v (64 where the rows are read in place or a
+    general geometry's tiles are dealt, which have no tile shapes)."""
     torch = _torch()
     if out is not None and out.dtype != torch.float32:
         raise TypeError("sinogram must be float32")
@@ -275,7 +277,9 @@ def set_forward_tile(geom: Geometry, dtype, tile_v: int, view_group: int = 8,
     loads), 64, 32 or 16 detector pixels along v per wavefront row (for 16-bit
     storage also 128: two pixels per lane), view_group views per tile turn
     (1..64), load_group planes whose loads a lane issues together (2 or 4);
-    tile_v = 0 forgets this process's choice."""
+    tile_v = 0 forgets this process's choice. Geometries whose rows are read in
+    place (circular scans with enough rays in a column) use view_group only, and
+    general ones whose tiles are dealt use none of the three."""
     torch = _torch()
     code = {torch.float32: F32, torch.bfloat16: BF16, torch.float16: F16}[dtype]
     check(lib().gjp_set_forward_tile(geom.handle, code, int(tile_v), int(view_group),
