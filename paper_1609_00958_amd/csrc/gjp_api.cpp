@@ -973,19 +973,31 @@ long long padded_elems(const int* n) {
 
 // Whether the row forward is the default, or there are too few rays in a column to share
 // its rows. In rows_per_lane's costs a wavefront of the copies' kernel takes 0.92 per 64
-// rays of the set tile; its two copies take 14 us and 6.5 ps per voxel: 64^3, 64 x 64
-// rays, 64 views 31 us, rows 22, 360 views 64 and 93. 16-bit rows cost a tenth more, 16-bit
-// copies less: 4 ps per voxel, and 0.83 where they fit the L2s (128^3, 200 views of 192 x
-// 128 286 us, rows 307; 256^3, 100 views of 384 x 128 726 and 657).
+// rays, of 16 bits 0.83 (BF16 0.95; both 1.17 where the copies exceed the L2s) and a 16-bit
+// row's a tenth more than an FP32 one's. The copies take a launch and 6.5 or 1.5 ps per
+// voxel on the device; a call with them is held up to 29 us by the host, however short, so
+// rows that end before 24 us pay (copies -> rows, us: 64^3, 64 views of 64 x 64 29 -> 22;
+// without that allocation 20 -> 22). Above it they pay by the device's time: 55 x 60 x 53,
+// 140 views of 70 x 60 30 and 39; 45 x 58 x 50, 123 views of 71 x 40, no allocation, 24 and
+// 33; FP16 69 x 84 x 66, 193 views of 100 x 81 77 and 85; BF16 122 x 99 x 106, 309 views of
+// 156 x 137 350 and 286; FP16 128^3, 200 views of 192 x 128 286 and 307; 256^3, 100 views of
+// 384 x 128 726 and 657. A set tile of several rays per lane leaves the copies' kernel
+// slower than this where rays lie a voxel apart (FP16 122 x 106 x 140, 57 views of 124 x 134
+// 160 and 65): rows up to 14 us more.
 bool rows_pay(const gjp_geometry* g, int dtype, int tile_v_log2) {
   const int tile = std::max(64, gjp::tile_v_pixels(tile_v_log2));
   const double waves = ceil((double)g->n_v / tile) * (tile / 64);
-  const double planes = (double)std::max(g->n[0], g->n[1]) * g->n_u * g->n_views;
+  const double planes = 28.0e-12 * std::max(g->n[0], g->n[1]) * g->n_u * g->n_views;
   const double voxels = (double)g->n[0] * g->n[1] * g->n[2];
-  if (dtype == GJP_F32)
-    return 28.0e-12 * planes * (g->rows_cost - 0.92 * waves) <= 14.0e-6 + 6.5e-12 * voxels;
-  const double wave = 8.0 * voxels <= 32.0 * 1024 * 1024 ? 0.83 : 1.17;  // both copies
-  return 28.0e-12 * planes * (1.1 * g->rows_cost - wave * waves) <= 14.0e-6 + 4.0e-12 * voxels;
+  const bool f32 = dtype == GJP_F32;
+  const double rows = planes * g->rows_cost * (f32 ? 1.0 : 1.1);
+  const double wave = f32                                      ? 0.92
+                      : 8.0 * voxels > 32.0 * 1024 * 1024      ? 1.17  // both copies
+                      : dtype == GJP_F16                       ? 0.83
+                                                               : 0.95;
+  const double more = rows - planes * wave * waves;
+  if (tile > 64) return more <= 14.0e-6 + (f32 ? 6.5e-12 : 4.0e-12) * voxels;
+  return rows <= 15.0e-6 || more <= (f32 ? 2.0e-6 + 6.5e-12 * voxels : 5.0e-6 + 1.5e-12 * voxels);
 }
 
 // Rays per lane of the row forward, or 0 where the padded copies are sampled.

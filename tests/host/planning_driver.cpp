@@ -479,6 +479,17 @@ static int dispatch_main() {
       gjp_destroy_geometry(g);
     }
   }
+  {  // half-filled wavefronts of rows: only where the call is over before the host is
+    const int m[3] = {45, 58, 50};
+    std::vector<double> w(12 * 123);
+    for (int n_views : {40, 123}) {
+      CHECK(gjp_views_circular_cone(n_views, 180, 270, 1.3, 2.0, 71, 40, w.data()) == GJP_OK);
+      g = make(m, GJP_CONE, n_views, 71, 40, w.data());
+      for (int dtype : {GJP_F32, GJP_BF16, GJP_F16})
+        CHECK(g && g->rows > 0 && rows_taken(g, dtype, 0) == (n_views == 40));
+      gjp_destroy_geometry(g);
+    }
+  }
   CHECK(gjp_views_parallel(30, 1, 1, 90, 80, v.data()) == GJP_OK);
   g = make(n, GJP_PARALLEL, 30, 90, 80, v.data());
   CHECK(g && g->separable && g->rows > 0 && g->tiles && !g->free_gather);
