@@ -330,10 +330,9 @@ __device__ __forceinline__ void project_column(const FwdArgs& a, const void* vol
       for (int j = 0; j < cnt; j += kSub) {
         // window of voxels that the rays span on the planes that the loop takes (up to
         // three past the last one's, whose rows read as zeros)
-        const int np = min(kSub, cnt - j);
         const double t0 = (double)(base + j) - sm;
         RowWindow win;
-        if (!row_window(A, B, C, D, t0, row_planes(np), last, n2, win)) continue;
+        if (!row_window(A, B, C, D, t0, row_planes(min(kSub, cnt - j)), last, n2, win)) continue;
         const int zd = __builtin_amdgcn_readfirstlane(win.zd);
         const int need = __builtin_amdgcn_readfirstlane(win.need);
         const int pad = __builtin_amdgcn_readfirstlane(win.pad);
@@ -342,6 +341,9 @@ __device__ __forceinline__ void project_column(const FwdArgs& a, const void* vol
           for (int k = 0; k < 2 * kRow / 256; ++k)
             reinterpret_cast<f4l*>(sh.row)[64 * k + lane] = f4l{0.0f, 0.0f, 0.0f, 0.0f};
         }
+        // (not kept from the window on: one scalar register too many, and FP16 with two
+        // rays per lane passed 96 vector registers, four instead of five wavefronts)
+        const int np = min(kSub, (int)here_u((uint32_t)cnt) - j);
         float gb[RPL], cb[RPL];
 #pragma unroll
         for (int r = 0; r < RPL; ++r) {
