@@ -18,11 +18,11 @@
 // voxel row pair and 64 RPL rays. What bounds the kernel: the vector ALUs and the
 // vector memory path together. At 512^3, 720 views of 768^2 a sample takes 12.4
 // instructions, seven of its own (three of half rate) and the rest its share of the
-// plane's; at two cycles each they fill 56% of the ALUs' time, at the rates measured
-// for them one by one 75-90%. The data unit is busy 99% of the time (a quarter of
+// plane's; at two cycles each they fill 55% of the ALUs' time, at the rates measured
+// for them one by one 75-90%. The data unit is busy 98% of the time (a quarter of
 // it waiting for L1: the rows come from L2, since the wavefronts of neighbouring
-// columns drift apart), the address unit 88%, LDS 62%. BF16, with half the bytes: 62,
-// 98, 83 and 59%, and 57 instead of 61 ms.
+// columns drift apart), the address unit 87%, LDS 62%. BF16, with half the bytes: 62,
+// 98, 83 and 59%, and 56 instead of 60.5 ms.
 // Measured steps, 256^3 / 360 views of 384^2: 4- and 8-byte loads 4.2 ms (the
 // return path gives 30 bytes per clock whatever their width below 16), 16-byte
 // loads 3.7 ms, the next planes' loads issued before the current ones are
